@@ -117,15 +117,49 @@ __global__ void __launch_bounds__(256) k_checksum(const unsigned *__restrict__ w
         __hip_atomic_fetch_add(out, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Sets *bad when any density value is not finite.
-__global__ void __launch_bounds__(256) k_check_finite(const float *__restrict__ rho, int64_t n,
-                                                      unsigned long long *__restrict__ bad)
+// Integer that orders like the float x (any sign), above 0 for every number.
+__device__ __forceinline__ unsigned ordered_bits(float x)
+{
+    const unsigned u = __float_as_uint(x);
+    return (u >> 31) ? ~u : u | 0x80000000u;
+}
+
+// out[0]: waves that saw a value that is not finite; out[1], out[2]: largest ordered_bits of the
+// values and of the negated values (the range of the density).
+__global__ void __launch_bounds__(256) k_check_density(const float *__restrict__ rho, int64_t n,
+                                                       unsigned long long *__restrict__ out)
 {
     bool ok = true;
+    float hi = -3.402823466e38f, lo = 3.402823466e38f;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) ok = ok && isfinite(rho[k]);
-    if (__ballot(!ok) != 0ull && (threadIdx.x & 63u) == 0)
-        __hip_atomic_fetch_add(bad, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) {
+        const float v = rho[k];
+        ok = ok && isfinite(v);
+        hi = fmaxf(hi, v);
+        lo = fminf(lo, v);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        hi = fmaxf(hi, __shfl_xor(hi, o, 64));
+        lo = fminf(lo, __shfl_xor(lo, o, 64));
+    }
+    const bool bad = __ballot(!ok) != 0ull;
+    __shared__ float sh[2][4];
+    __shared__ int sbad[4];
+    if ((threadIdx.x & 63u) == 0) {
+        sh[0][threadIdx.x >> 6] = hi;
+        sh[1][threadIdx.x >> 6] = lo;
+        sbad[threadIdx.x >> 6] = bad;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        hi = fmaxf(fmaxf(sh[0][0], sh[0][1]), fmaxf(sh[0][2], sh[0][3]));
+        lo = fminf(fminf(sh[1][0], sh[1][1]), fminf(sh[1][2], sh[1][3]));
+        if (sbad[0] | sbad[1] | sbad[2] | sbad[3])
+            __hip_atomic_fetch_add(out, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        atomicMax(out + 1, (unsigned long long)ordered_bits(hi));
+        atomicMax(out + 2, (unsigned long long)ordered_bits(-lo));
+    }
 }
 
 __global__ void __launch_bounds__(256) k_clear_u64(unsigned long long *p, int64_t n)
@@ -162,13 +196,13 @@ int launch_field_checksum(const void *field, size_t bytes, unsigned long long *o
     return (int)hipGetLastError();
 }
 
-int launch_check_finite(const float *rho, int64_t n, unsigned long long *bad, hipStream_t stream)
+int launch_check_density(const float *rho, int64_t n, unsigned long long *out, hipStream_t stream)
 {
-    int e = launch_clear_u64(bad, 1, stream);
+    int e = launch_clear_u64(out, 3, stream);
     if (e || n <= 0) return e;
     int64_t blocks = (n + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_check_finite, dim3((unsigned)blocks), dim3(256), 0, stream, rho, n, bad);
+    if (blocks > 2048) blocks = 2048;
+    hipLaunchKernelGGL(k_check_density, dim3((unsigned)blocks), dim3(256), 0, stream, rho, n, out);
     return (int)hipGetLastError();
 }
 

@@ -127,22 +127,19 @@ void fill_params(const pbr_ctx *ctx, const Derived &d, double ds, TraceParams *o
         P.hi[a] = ctx->origin[a] + (double)(n3[a] - 1) * ctx->spacing[a];
         P.step_cell[a] = P.h / ctx->spacing[a];
     }
-    // FP32 step constants (see TraceParams): each a float operation on float values, so that a
-    // partial step of fraction 1 forms the same bits on the device
-    float tlim = 3.0e38f;
     for (int a = 0; a < 3; ++a) {
+        P.step2_cell[a] = P.h * P.step_cell[a];
         P.g32[a] = (float)P.step_cell[a];
-        P.gh32[a] = 0.5f * P.g32[a];
-        const double k = std::ceil(1.05 * (double)P.g32[a] + 4.0e-3);
-        P.kin[a] = k < 1.0 ? 1 : (k > 1.0e6 ? 1000000 : (int)k);
-        const float t = ((float)P.kin[a] - 4.0e-3f) / P.g32[a];
-        tlim = t < tlim ? t : tlim;
     }
-    P.h32 = (float)P.h;
-    P.h4_32 = 0.25f * P.h32;
-    P.h2_32 = 0.5f * P.h32;
-    P.h6_32 = P.h32 * (1.0f / 6.0f);
-    P.tlim32 = tlim;
+    // |D| = |n grad n| anywhere in the box, from the range of the density: a node's derivative is at
+    // most twice the range over the spacing (the one-sided difference on a face, -3/2, 2, -1/2)
+    double slope2 = 0.0;
+    for (int a = 0; a < 3; ++a) {
+        const double q = 2.0 * ctx->K * (ctx->rho_max - ctx->rho_min) / ctx->spacing[a];
+        slope2 += q * q;
+    }
+    const double n_top = 1.0 + ctx->K * std::fmax(std::fabs(ctx->rho_min), std::fabs(ctx->rho_max));
+    P.bend32 = (float)(1.001 * pbr::kRunSteps * P.h * n_top * std::sqrt(slope2));
     P.n_inf = d.n_inf;
     P.z_lens = ctx->has_chain ? ctx->chain.aim_z : ctx->optics.z_front_vertex;
     P.a = d.a; P.R = d.R; P.t = d.t; P.clear = d.clear; P.n_glass = ctx->optics.n_glass;
@@ -329,6 +326,15 @@ size_t pbr_field_workspace_bytes_nodes(int nx, int ny, int nz)
 }
 
 namespace {
+// Inverse of the density check's ordered_bits.
+float float_of_ordered_bits(unsigned u)
+{
+    u = (u >> 31) ? u & 0x7FFFFFFFu : ~u;
+    float x;
+    std::memcpy(&x, &u, 4);
+    return x;
+}
+
 int set_field(pbr_ctx *ctx, const float *rho_dev, int nx, int ny, int nz, const double origin[3],
               const double spacing[3], double K, double rho_inf, void *ws_dev, size_t ws_bytes, bool nodes)
 {
@@ -348,17 +354,20 @@ int set_field(pbr_ctx *ctx, const float *rho_dev, int nx, int ny, int nz, const 
     if (((uintptr_t)ws_dev & 15u) != 0) return fail(ctx, PBR_ERR_ARG, "field workspace must be 16-byte aligned");
     const pbr::FieldLayout L = pbr::field_layout(nx, ny, nz, nodes);
     char *base = (char *)ws_dev;
+    double rho_min = 0.0, rho_max = 0.0;
     if (ctx->device >= 0) {
         DeviceGuard g(ctx->device);
         if (!g.ok) return fail(ctx, PBR_ERR_HIP, "hipSetDevice failed");
         // every density value must be finite: checked on the device before anything is prepared
         {
-            unsigned long long *slot = ctx->counters + pbr::CNT_QUEUE + 2, bad = 0;
-            int e = pbr::launch_check_finite(rho_dev, (int64_t)nx * ny * nz, slot, ctx->stream);
-            if (!e) e = (int)hipMemcpyAsync(&bad, slot, 8, hipMemcpyDeviceToHost, ctx->stream);
+            unsigned long long *slot = ctx->counters + pbr::CNT_QUEUE + 2, got[3] = {0, 0, 0};
+            int e = pbr::launch_check_density(rho_dev, (int64_t)nx * ny * nz, slot, ctx->stream);
+            if (!e) e = (int)hipMemcpyAsync(got, slot, sizeof got, hipMemcpyDeviceToHost, ctx->stream);
             if (!e) e = (int)hipStreamSynchronize(ctx->stream);
             if (e) return hip_fail(ctx, e, "density check");
-            if (bad) return fail(ctx, PBR_ERR_ARG, "the density grid holds non-finite values");
+            if (got[0]) return fail(ctx, PBR_ERR_ARG, "the density grid holds non-finite values");
+            rho_max = float_of_ordered_bits((unsigned)got[1]);
+            rho_min = -float_of_ordered_bits((unsigned)got[2]);
         }
         // brick max |grad n| and FP64 flags start at zero (fill kernel, no memset node)
         int e = pbr::launch_clear_u64((unsigned long long *)(base + L.gmax_off),
@@ -377,6 +386,8 @@ int set_field(pbr_ctx *ctx, const float *rho_dev, int nx, int ny, int nz, const 
     for (int a = 0; a < 3; ++a) { ctx->origin[a] = origin[a]; ctx->spacing[a] = spacing[a]; }
     ctx->K = K;
     ctx->rho_inf = rho_inf;
+    ctx->rho_min = rho_min;
+    ctx->rho_max = rho_max;
     ctx->has_field = true;
     ++ctx->scene_version;
     ++ctx->param_version;

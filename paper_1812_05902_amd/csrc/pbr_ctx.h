@@ -32,6 +32,7 @@ struct pbr_ctx {
     int nx = 0, ny = 0, nz = 0;
     double origin[3] = {0, 0, 0}, spacing[3] = {0, 0, 0};
     double K = 0.0, rho_inf = 0.0;
+    double rho_min = 0.0, rho_max = 0.0;    // range of the density grid
     // optics
     bool has_optics = false;
     bool has_chain = false;                 // a general optical chain replaces the singlet
@@ -111,8 +112,9 @@ int emit_and_trace_impl(pbr_ctx *ctx, const float *src_dev, int64_t n_src, int32
 
 }  // namespace host
 
-// Counts into *bad (device) the waves that saw a non-finite density value, field_prep.hip.
-int launch_check_finite(const float *rho, int64_t n, unsigned long long *bad, hipStream_t stream);
+// out (device, 3 words): the number of waves that saw a non-finite density value, then the largest
+// ordered_bits() of the values and of the negated values, field_prep.hip.
+int launch_check_density(const float *rho, int64_t n, unsigned long long *out, hipStream_t stream);
 // Order-independent checksum of a device buffer's 32-bit words into *out (device), field_prep.hip.
 int launch_field_checksum(const void *field, size_t bytes, unsigned long long *out, hipStream_t stream);
 

@@ -111,16 +111,10 @@ struct TraceParams {
     int pad1;
     // general optical chain (null: the singlet above)
     const pbr_optical_chain *chain;
-    // FP32 constants of a full integration step, rounded once on the host from h and step_cell so
-    // that the kernels hold them in scalar registers: g = h / spacing, g / 2, h, h / 4, h / 2,
-    // h * (1/6) (float products, as the partial steps form them).  kin: per axis the cells a full
-    // step may cross when |T| <= 1.05 (any gas), ceil(1.05 g + 4e-3) and at least 1; tlim32: min
-    // over the axes of (kin - 4e-3) / g, the largest |T| component for which a full step from a
-    // cell at least kin cells from both faces ends 4e-3 cells inside the box (see the integration
-    // kernel)
-    float g32[3], gh32[3];
-    float h32, h4_32, h2_32, h6_32, tlim32;
-    int kin[3];
+    // integration steps: h^2 / spacing; h / spacing in FP32; a bound on the change of any component of
+    // T over kRunSteps full steps, from the range of the density (see run_budget)
+    double step2_cell[3];
+    float g32[3], bend32;
 };
 
 // Offset of the optical chain inside the context's 4 KiB device block (counters come first).
@@ -223,6 +217,9 @@ struct ChunkHook {
                TraceList *list);
     void *self;
 };
+
+// Full steps an integration kernel takes between two tests of the box faces (at most).
+constexpr int kRunSteps = 32;
 
 constexpr int kTile = 32;  // deposit pre-aggregation tile of single-image traces (pixels per side, in LDS)
 

@@ -43,15 +43,6 @@ __device__ __forceinline__ bool access_ok(const TraceParams &P, bool ok)
 #endif
 }
 
-// x clamped to [0, hi] in one instruction (for a bound that is not a constant the compiler emits a
-// max and a min); hi is uniform across the wave.
-__device__ __forceinline__ int clamp_index(int x, int hi)
-{
-    int r;
-    asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(x), "s"(hi));
-    return r;
-}
-
 // A stage-point coordinate x (cell units, relative to the ray's cell) split into the whole cells it
 // lies ahead, floor(x), and the fraction x - floor(x) inside that cell.  For float two instructions
 // (v_cvt_flr_i32_f32 saturates out-of-range values; v_fract_f32 keeps the fraction below 1).
@@ -70,12 +61,11 @@ template <> __device__ __forceinline__ int split_cell<double>(double x, double &
     return (int)o;
 }
 
-// The coefficients (cell layout) or corner values (node layout) of the cell the ray is in, held
-// in registers: a stage point only gathers
-// from memory when it lies in another cell (about once per cell crossing, since the three stage
-// points of a step run ahead of the ray).
+// The coefficients (cell layout) or corner values (node layout) of one cell, the ray's base cell,
+// held in registers.  A ray's position is kept as the integer base cell and a fraction relative to
+// it; a stage point whose fractions all lie in [0, 1) is sampled from the registers as it is, and
+// only a point outside moves the base to its cell (enter_cell).
 struct CellCache {
-    int ix, iy, iz;  // the cached cell, ix = -1: none
     float4 c[kCellFloat4];
 };
 
@@ -83,9 +73,9 @@ struct CellCache {
 // 101, 011, 111 (x, y, z offsets), loaded into the cache.  They are interpolated as they are (see
 // sample_field): steps in the fine grids this layout serves cross a cell every one or two
 // samples, so a per-gather transform into polynomial coefficients would cost more than it saves.
-// A move to a face neighbour of the cached cell keeps the four corners of the shared face and
-// loads the other four: half the gather traffic on most crossings.
-__device__ __forceinline__ void gather_nodes(const TraceParams &P, const int ic[3], CellCache &cc)
+// d: ic minus the cached cell.  A move to a face neighbour keeps the four corners of the shared face
+// and loads the other four: half the gather traffic on most crossings.
+__device__ __forceinline__ void gather_nodes(const TraceParams &P, const int ic[3], const int d[3], CellCache &cc)
 {
     const size_t sy = (size_t)P.nx, sz = (size_t)P.nx * (size_t)P.ny;
     {   // Every gathering lane wants the same cell (about a quarter of the gathers on the Tomo-PIV
@@ -106,8 +96,8 @@ __device__ __forceinline__ void gather_nodes(const TraceParams &P, const int ic[
     }
     const float4 *b = P.cells + (size_t)ic[2] * sz + (size_t)ic[1] * sy + (size_t)ic[0];
     float4 *c = cc.c;
-    const int dx = ic[0] - cc.ix, dy = ic[1] - cc.iy, dz = ic[2] - cc.iz;
-    const bool one = cc.ix >= 0 && abs(dx) + abs(dy) + abs(dz) == 1;  // ix = -1: nothing cached
+    const int dx = d[0], dy = d[1], dz = d[2];
+    const bool one = abs(dx) + abs(dy) + abs(dz) == 1;
     if (one && dz == 1) {
         c[0] = c[3]; c[1] = c[5]; c[2] = c[6]; c[4] = c[7];
         c[3] = b[sz]; c[5] = b[sz + 1]; c[6] = b[sz + sy]; c[7] = b[sz + sy + 1];
@@ -139,13 +129,14 @@ __device__ __forceinline__ void gather_nodes(const TraceParams &P, const int ic[
 // same bytes, which is what the texture-data path spends its time on, and costs more vector and
 // scalar instructions; what it does save is registers, so the kernels that also hold FP64 steps
 // (mixed precision, calibration) use it: four waves per SIMD instead of three.
-__device__ __forceinline__ void gather_nodes_deferred(const TraceParams &P, const int ic[3], CellCache &cc)
+__device__ __forceinline__ void gather_nodes_deferred(const TraceParams &P, const int ic[3], const int d[3],
+                                                      CellCache &cc)
 {
     const size_t sy = (size_t)P.nx, sz = (size_t)P.nx * (size_t)P.ny;
     const float4 *b = P.cells + (size_t)ic[2] * sz + (size_t)ic[1] * sy + (size_t)ic[0];
     float4 *c = cc.c;
-    const int dx = ic[0] - cc.ix, dy = ic[1] - cc.iy, dz = ic[2] - cc.iz;
-    const bool near = cc.ix >= 0 && (unsigned)(dx + 1) <= 2u && (unsigned)(dy + 1) <= 2u && (unsigned)(dz + 1) <= 2u;
+    const int dx = d[0], dy = d[1], dz = d[2];
+    const bool near = (unsigned)(dx + 1) <= 2u && (unsigned)(dy + 1) <= 2u && (unsigned)(dz + 1) <= 2u;
     // corners of the new cell that the cached cell does not hold: slot bits of the x = 1 corners
     // (1, 4, 5, 7), the x = 0 corners (0, 2, 3, 6), likewise for y and z
     unsigned need = 0xFFu;
@@ -183,63 +174,92 @@ __device__ __forceinline__ void gather_nodes_deferred(const TraceParams &P, cons
     if (need & 0x80u) c[7] = b[sz + sy + 1];
 }
 
-// Trilinear interpolation of (n - 1, grad n) at the point (cell c, fraction f); the fraction may
-// lie outside [0, 1) (stage points of eq. 5), in which case the point is moved into the cell that
-// holds it and then onto the box.  Returns n, writes G = grad n (D = n G, eq. 6, is formed by the
-// caller, folded into the step's sums).
-// INSIDE: the caller has shown that the point lies inside the box and that the ray's own cell index
-// is a cell of the grid (see trace_step), so the edge extension is left out; a stage point's cell
-// index is still clamped to the grid, which keeps every gather in bounds whatever the values.
-// NODES: the field is stored per node (see gather_nodes); compiled into dedicated kernels only.
-template <typename F, bool AT_STATE = false, bool INSIDE = false, int NODES = 0>
-__device__ __forceinline__ F sample_field(const TraceParams &P, CellCache &cc, const int c[3],
-                                          const F f[3], F G[3])
+// Loads cell ic into the cache; d: ic minus the cached cell (any large value when nothing is
+// cached).  NODES: 0 per-cell records, 1 and 2 the node layout (its two gathers).
+template <int NODES>
+__device__ __forceinline__ void gather_cell(const TraceParams &P, const int ic[3], const int d[3], CellCache &cc)
+{
+    if (NODES == 2) gather_nodes_deferred(P, ic, d, cc);
+    else if (NODES) gather_nodes(P, ic, d, cc);
+    else {
+        const int key = (ic[2] * (P.ny - 1) + ic[1]) * (P.nx - 1) + ic[0];
+        const float4 *p = P.cells + (size_t)key * kCellFloat4;
+#pragma unroll
+        for (int m = 0; m < kCellFloat4; ++m) cc.c[m] = p[m];
+    }
+}
+
+// The first cell of a ray (c inside the grid).
+template <int NODES>
+__device__ __forceinline__ void first_cell(const TraceParams &P, int c[3], CellCache &cc)
+{
+    if (PBR_CHECKED && !access_ok(P, (unsigned)c[0] <= (unsigned)(P.nx - 2) && (unsigned)c[1] <= (unsigned)(P.ny - 2) &&
+                                         (unsigned)c[2] <= (unsigned)(P.nz - 2))) {
+        c[0] = min(max(c[0], 0), P.nx - 2);
+        c[1] = min(max(c[1], 0), P.ny - 2);
+        c[2] = min(max(c[2], 0), P.nz - 2);
+    }
+    const int far[3] = {1 << 20, 0, 0};
+    gather_cell<NODES>(P, c, far, cc);
+}
+
+// One word per fraction that orders like it for values >= 0 and is large for negative ones and NaN,
+// and its value at 1: x lies in [0, 1) exactly if unit_word(x) < unit_one.
+__device__ __forceinline__ unsigned unit_word(float x) { return __float_as_uint(x); }
+__device__ __forceinline__ unsigned unit_word(double x) { return (unsigned)__double2hiint(x); }
+template <typename F> struct UnitOne { static constexpr unsigned value = 0x3F800000u; };
+template <> struct UnitOne<double> { static constexpr unsigned value = 0x3FF00000u; };
+
+// A point q (relative to the base cell c) outside the base cell: the base moves to the cell that
+// holds the point (its record is gathered, the ray's own position fd, f becomes relative to it) and
+// q becomes the fraction inside that cell.  The index is clamped to the grid, which keeps every
+// gather in bounds whatever the values.  EDGE: the point may lie outside the box; it is then moved
+// onto it.
+template <typename F, bool EDGE, int NODES>
+__device__ __forceinline__ void enter_cell(const TraceParams &P, CellCache &cc, int c[3], double fd[3], F f[3], F q[3])
 {
     const int nmax[3] = {P.nx - 2, P.ny - 2, P.nz - 2};
-    int ic[3];
-    F w[3];
+    int ic[3], d[3];
+    bool off = false;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        int i0;
-        F t;
-        if (AT_STATE) {
-            // the ray's own position: fraction already in [0, 1], cell normally valid
-            i0 = c[a];
-            t = f[a];
-        } else {
-            // stage point: fraction anywhere.  Inside the box the point is finite (see trace_step);
-            // elsewhere NaN becomes finite first (fmax/fmin return the number)
-            const F fa = INSIDE ? f[a] : fmin(fmax(f[a], (F)(-1.0e6)), (F)(1.0e6));
-            i0 = c[a] + split_cell<F>(fa, t);
-        }
-        // (every step starts in a cell of the grid, so an inside step's own index needs no clamp)
-        const int i = INSIDE ? (AT_STATE ? i0 : clamp_index(i0, nmax[a])) : min(max(i0, 0), nmax[a]);
-        if (!INSIDE) {
-            t = i0 < 0 ? (F)0 : t;
-            t = i0 > nmax[a] ? (F)1 : t;
-        }
-        ic[a] = i;
-        w[a] = t;
+        // NaN becomes finite first where the point is not known to be (fmax/fmin return the number)
+        const F x = EDGE ? fmin(fmax(q[a], (F)(-1.0e6)), (F)(1.0e6)) : q[a];
+        d[a] = split_cell<F>(x, q[a]);
+        ic[a] = c[a] + d[a];
+        off = off | ((unsigned)ic[a] > (unsigned)nmax[a]);
     }
-    // compare cell coordinates (no index arithmetic unless the cell changed)
-    if ((ic[0] != cc.ix) | (ic[1] != cc.iy) | (ic[2] != cc.iz)) {
+    if (__builtin_expect(off, 0)) {  // outside the grid, or on an upper face (fraction 1 of the last cell)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int i = min(max(ic[a], 0), nmax[a]);
+            if (EDGE) q[a] = ic[a] < 0 ? (F)0 : q[a];
+            q[a] = ic[a] > nmax[a] ? (F)1 : q[a];
+            ic[a] = i;
+            d[a] = i - c[a];
+        }
+    }
+    if ((d[0] | d[1] | d[2]) != 0) {
         if (PBR_CHECKED && !access_ok(P, (unsigned)ic[0] <= (unsigned)nmax[0] && (unsigned)ic[1] <= (unsigned)nmax[1] &&
                                              (unsigned)ic[2] <= (unsigned)nmax[2])) {
 #pragma unroll
             for (int a = 0; a < 3; ++a) ic[a] = min(max(ic[a], 0), nmax[a]);
         }
-        if (NODES == 2) gather_nodes_deferred(P, ic, cc);
-        else if (NODES) gather_nodes(P, ic, cc);
-        else {
-            const int key = (ic[2] * (P.ny - 1) + ic[1]) * (P.nx - 1) + ic[0];
-            const float4 *p = P.cells + (size_t)key * kCellFloat4;
+        gather_cell<NODES>(P, ic, d, cc);
 #pragma unroll
-            for (int m = 0; m < kCellFloat4; ++m) cc.c[m] = p[m];
+        for (int a = 0; a < 3; ++a) {
+            c[a] = ic[a];
+            fd[a] -= (double)d[a];
+            f[a] = (F)fd[a];
         }
-        cc.ix = ic[0];
-        cc.iy = ic[1];
-        cc.iz = ic[2];
     }
+}
+
+// Trilinear interpolation of (n - 1, grad n) at fractions w of the cached cell.  Returns n - 1, writes
+// G = grad n (D = n G, eq. 6, is formed by the caller).
+template <typename F, int NODES>
+__device__ __forceinline__ F interpolate(const CellCache &cc, const F w[3], F G[3])
+{
     const F x = w[0], y = w[1], z = w[2];
     F v[4];
     if (NODES) {
@@ -278,111 +298,126 @@ __device__ __forceinline__ F sample_field(const TraceParams &P, CellCache &cc, c
     G[0] = v[1];
     G[1] = v[2];
     G[2] = v[3];
-    return (F)1 + v[0];
+    return v[0];
 }
 
-// Margin (cells) that a full step taken without the edge extension keeps from every face.
+// The field at the point q relative to the base cell (fractions anywhere): see enter_cell and
+// interpolate.  Whether the point has left the base cell is one maximum and one compare over all
+// three axes, where finding its cell from scratch takes five slow instructions per axis.
+template <typename F, bool EDGE, int NODES>
+__device__ __forceinline__ F sample_field(const TraceParams &P, CellCache &cc, int c[3], double fd[3], F f[3], F q[3],
+                                          F G[3])
+{
+    const unsigned m = max(max(unit_word(q[0]), unit_word(q[1])), unit_word(q[2]));
+    if (m >= UnitOne<F>::value) enter_cell<F, EDGE, NODES>(P, cc, c, fd, f, q);
+    if (sizeof(F) == sizeof(double) && NODES == 2) {
+#pragma unroll
+        for (int k = 0; k < kCellFloat4; ++k)
+            asm volatile("" : "+v"(cc.c[k].x), "+v"(cc.c[k].y), "+v"(cc.c[k].z), "+v"(cc.c[k].w));
+    }
+    return interpolate<F, NODES>(cc, q, G);
+}
+
+// Margin (cells) that the steps of a run keep from every face they move towards.
 constexpr float kFaceMargin = 1.0e-3f;
 
 // Per-launch constants of the integration loop.
 template <typename F> struct StepGeom {
-    F g[3], gh[3];     // h / spacing (cell units per unit of T in a full step), half of it
-    F hstep, h4, h2, h6;  // h, h / 4, h / 2, h * (1/6)
-    int last[3];       // n - 1 per axis (the upper face, in cells)
-    int lo[3];         // interior margin k: cells a full step may cross
-    unsigned bnd[3];   // max(n - 1 - 2k, 0): interior cells are k <= c < k + bnd
-    F tlim;            // largest |T| component for which a full step crosses fewer than k - 4 kFaceMargin cells
+    F s[3];        // h^2 / spacing: cells per full step squared, per unit of D
+    int last[3];   // n - 1 per axis (the upper face, in cells)
 };
 
-template <typename F> __device__ __forceinline__ StepGeom<F> step_geom(const TraceParams &P);
-// FP32: the constants the host rounded once (uniform: scalar registers)
-template <> __device__ __forceinline__ StepGeom<float> step_geom<float>(const TraceParams &P)
+template <typename F> __device__ __forceinline__ StepGeom<F> step_geom(const TraceParams &P)
 {
-    StepGeom<float> s;
+    StepGeom<F> sg;
     const int nn[3] = {P.nx, P.ny, P.nz};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        s.g[a] = P.g32[a];
-        s.gh[a] = P.gh32[a];
-        s.last[a] = nn[a] - 1;
-        s.lo[a] = P.kin[a];
-        s.bnd[a] = (unsigned)max(nn[a] - 1 - 2 * P.kin[a], 0);
+        sg.s[a] = (F)P.step2_cell[a];
+        // an FP32 operation with a scalar-register operand issues at half the rate of one on vector
+        // registers alone (4.4 against 2.7 cycles per wave measured): the constants of every sample
+        // stay in vector registers
+        if (sizeof(F) == sizeof(float)) asm("" : "+v"(sg.s[a]));
+        sg.last[a] = nn[a] - 1;
     }
-    s.hstep = P.h32;
-    s.h4 = P.h4_32;
-    s.h2 = P.h2_32;
-    s.h6 = P.h6_32;
-    s.tlim = P.tlim32;
-    return s;
-}
-template <> __device__ __forceinline__ StepGeom<double> step_geom<double>(const TraceParams &P)
-{
-    StepGeom<double> s;
-    const int nn[3] = {P.nx, P.ny, P.nz};
-    s.tlim = 3.0e38;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        s.g[a] = P.step_cell[a];
-        s.gh[a] = 0.5 * s.g[a];
-        s.last[a] = nn[a] - 1;
-        s.lo[a] = P.kin[a];
-        s.bnd[a] = (unsigned)max(nn[a] - 1 - 2 * P.kin[a], 0);
-        s.tlim = fmin(s.tlim, ((double)P.kin[a] - 4.0 * (double)kFaceMargin) / s.g[a]);
-    }
-    s.hstep = P.h;
-    s.h4 = 0.25 * P.h;
-    s.h2 = 0.5 * P.h;
-    s.h6 = P.h * (1.0 / 6.0);
-    return s;
+    return sg;
 }
 
-// One step of eqs. 3 and 5 of length lam * h in the parameter t (dR/dt = T, dT/dt = D), in
-// cell units: g[a] = h / spacing[a].  The cell fraction fd is accumulated in FP64: its increment
-// is nearly the same every step, so FP32 rounding of the running sum would err the same way
-// every step and grow linearly with the step count.  Stage points are formed in F.
-// With D_A, D_B, D_C the values of D = n grad n at the three stage points, so that eq. 5's
-// A = h D_A, B = h D_B, C = h D_C, the sums are regrouped without forming A, B, C:
-//   stage B point  R + (h/2) (T + (h/4) D_A)        (= R + h (T/2 + A/8))
-//   stage C point  R + h (T + (h/2) D_B)            (= R + h (T + B/2))
-//   R'             R + h (T + (h/6) (D_A + 2 D_B))  (= R + h (T + (A + 2B)/6))
-//   T'             T + (h/6) (D_A + 4 D_B + D_C)    (= T + (A + 4B + C)/6)
-// A partial step (lam = 1) and a full step form the same constants and give the same bits.
-// INSIDE: every point of the step is known to lie inside the box (full steps only).
-template <typename F, bool FULL, bool INSIDE = false, int NODES = 0>
-__device__ __forceinline__ void rkn_step(const TraceParams &P, CellCache &cc, int c[3], double fd[3],
-                                         const F Tr[3], F dT[3], const StepGeom<F> &sg, F lam)
+// The acceleration at the end point of the step before, when that step's last sample serves for it
+// (see rkn_step).
+template <typename F> struct StageCarry {
+    F aA[3];
+    bool have;
+};
+
+// Largest difference (cells) between the last stage point of a step and its end point for which the
+// sample of the one serves for the other: half the rounding of a stage point's own fraction.
+constexpr float kReuse = 0x1p-25f;
+
+// One step of eqs. 3 and 5 of length lam * h in the parameter t (dR/dt = T, dT/dt = D), in cells and
+// full steps: W = h T / spacing (cells per step) and a = h^2 D / spacing (cells per step squared),
+// D = n grad n at the stage points, so that the step length and the spacing drop out of the sums:
+//   stage B point  R + (W + a_A / 4) / 2             (= R + h (T/2 + A/8))
+//   stage C point  R + W + a_B / 2                   (= R + h (T + B/2))
+//   R'             R + W + (a_A + 2 a_B) / 6         (= R + h (T + (A + 2B)/6))
+//   W'             W + (a_A + 4 a_B + a_C) / 6       (= T + (A + 4B + C)/6)
+// The position fd (relative to the base cell) is accumulated in FP64: its increment is nearly the
+// same every step, so FP32 rounding of the running sum would err the same way every step and grow
+// linearly with the step count.  Stage points are formed in F, from f = (F)fd.  W = Wr + dW, Wr its
+// value at the entry: the small increments are summed into a small number.
+// EDGE: points of the step may lie outside the box (see enter_cell).
+// The stage C point and R' differ by (a_B - a_A) / 6.  In FP32, where that is at most kReuse on
+// every axis, a_C is also the next step's a_A, which saves a third of the samples: nearly all of
+// them in fields as smooth as the turbulence, all but those within the shock in the shock's.  The
+// kernel is bound by VALU issue, where a sample costs 34 instructions and this test five.
+template <typename F, bool FULL, bool EDGE, int NODES>
+__device__ __forceinline__ void rkn_step(const TraceParams &P, CellCache &cc, int c[3], double fd[3], F f[3],
+                                         const F Wr[3], F dW[3], StageCarry<F> &carry, const StepGeom<F> &sg, F lam)
 {
-    const F hh = FULL ? sg.hstep : lam * sg.hstep;
-    const F h4 = FULL ? sg.h4 : (F)0.25 * hh, h2 = FULL ? sg.h2 : (F)0.5 * hh;
-    const F h6 = FULL ? sg.h6 : hh * ((F)1 / (F)6);
-    F f[3], gg[3], gh[3], T[3], G[3], q[3], DA[3], DB[3];
+    constexpr F sixth = (F)1 / (F)6;
+    F W[3], acc[3], q[3], aA[3], step[3], sum[3];
+    // a = (h^2 / spacing) n grad n at q
+    auto sample = [&](F out[3]) {
+        F G[3];
+        const F dn = sample_field<F, EDGE, NODES>(P, cc, c, fd, f, q, G);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) out[a] = (sg.s[a] + sg.s[a] * dn) * G[a];
+    };
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
+        W[a] = Wr[a] + dW[a];
+        aA[a] = carry.aA[a];
+    }
+    if (sizeof(F) == sizeof(double) || !carry.have) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) q[a] = f[a];
+        sample(aA);
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        q[a] = FULL ? f[a] + (F)0.5 * (W[a] + (F)0.25 * aA[a]) : f[a] + (F)0.5 * lam * (W[a] + (F)0.25 * lam * aA[a]);
+    sample(acc);
+    // a_A and a_B only through their sums from here on
+    F e = (F)0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        q[a] = FULL ? f[a] + (W[a] + (F)0.5 * acc[a]) : f[a] + lam * (W[a] + (F)0.5 * lam * acc[a]);
+        if (sizeof(F) == sizeof(float)) e = fmax(e, fabs(acc[a] - aA[a]));
+        const F s2 = aA[a] + (F)2 * acc[a];
+        step[a] = FULL ? W[a] + sixth * s2 : lam * (W[a] + sixth * lam * s2);
+        sum[a] = aA[a] + (F)4 * acc[a];
+    }
+    sample(aA);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        fd[a] += (double)step[a];
         f[a] = (F)fd[a];
-        gg[a] = FULL ? sg.g[a] : lam * sg.g[a];
-        gh[a] = FULL ? sg.gh[a] : (F)0.5 * gg[a];
-        T[a] = Tr[a] + dT[a];
+        dW[a] = dW[a] + (FULL ? sixth : sixth * lam) * (aA[a] + sum[a]);
     }
-    F n = sample_field<F, true, INSIDE, NODES>(P, cc, c, f, G);
+    if (sizeof(F) == sizeof(float)) {
+        carry.have = e <= (F)(6.0f * kReuse);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        DA[a] = n * G[a];
-        q[a] = f[a] + gh[a] * (T[a] + h4 * DA[a]);
-    }
-    n = sample_field<F, false, INSIDE, NODES>(P, cc, c, q, G);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        DB[a] = n * G[a];
-        q[a] = f[a] + gg[a] * (T[a] + h2 * DB[a]);
-    }
-    n = sample_field<F, false, INSIDE, NODES>(P, cc, c, q, G);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        fd[a] += (double)(gg[a] * (T[a] + h6 * (DA[a] + (F)2 * DB[a])));
-        dT[a] = dT[a] + h6 * (n * G[a] + (DA[a] + (F)4 * DB[a]));
-        const double o = floor(fd[a]);
-        c[a] += (int)o;
-        fd[a] -= o;
+        for (int a = 0; a < 3; ++a) carry.aA[a] = aA[a];
     }
 }
 
@@ -391,100 +426,100 @@ template <typename T> __device__ __forceinline__ T pick3(const T v[3], int k)
     return k == 0 ? v[0] : (k == 1 ? v[1] : v[2]);
 }
 
+// Full steps (at most kRunSteps) the ray can take before any point of a step comes within kFaceMargin
+// cells of a face the ray may move towards; 0: the exit rule decides.  No component of T changes by
+// more than P.bend32 in kRunSteps steps (a bound on |D| from the range of the density), so the
+// path of the run lies between the straight lines of T - bend and T + bend; the stage points lie
+// between the same lines.  A field steep enough to leave no step within that bound is tried with the
+// bound for one step.
+template <typename F>
+__device__ __forceinline__ int run_budget(const TraceParams &P, const StepGeom<F> &sg, const int c[3], const double fd[3],
+                                          const F Wr[3], const F dW[3], int steps)
+{
+    float W[3], lo[3], hi[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        W[a] = (float)(Wr[a] + dW[a]);
+        lo[a] = ((float)c[a] + (float)fd[a]) - kFaceMargin;
+        hi[a] = ((float)(sg.last[a] - c[a]) - (float)fd[a]) - kFaceMargin;
+    }
+    // a direction that is not a number (or far beyond the grid in one step) takes the exit rule
+    if (!(fabsf(W[0]) + fabsf(W[1]) + fabsf(W[2]) < 1.0e6f)) return 0;
+    auto reach = [&](float bend) {
+        float k = (float)kRunSteps;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float b = P.g32[a] * bend, up = W[a] + b, dn = b - W[a];
+            if (up > 0.0f) k = fminf(k, hi[a] * __builtin_amdgcn_rcpf(up));
+            if (dn > 0.0f) k = fminf(k, lo[a] * __builtin_amdgcn_rcpf(dn));
+        }
+        return (int)floorf(k * 0.99999f);
+    };
+    int k = reach(P.bend32);
+    if (k < 1) k = min(reach(P.bend32 * (1.0f / (float)kRunSteps)), 1);
+    return min(k, P.max_steps + 1 - steps);
+}
+
 // Exit rule: before each step find the smallest straight-line step fraction lam at which the ray
 // reaches a face it moves towards; if lam <= 1 take one step of lam (when lam > 0), then move
 // straight along the new T onto that face.  (Per-axis values are selected with pick3 / unrolled
 // loops: no dynamically indexed arrays.)
 enum : int { STEP_GO = 0, STEP_EXIT = 1, STEP_LIMIT = 2 };
 
-// One iteration of the integration: a full step, or (when the straight line of a full step reaches
-// a face the ray moves towards) the partial step of fraction lam and, if the ray still heads out,
-// the straight move onto that face.  Returns STEP_EXIT when the ray left the box, STEP_LIMIT when
-// it ran out of steps, STEP_GO otherwise.
-// A full step taken by a ray in an interior cell (at least k cells from both faces on every axis,
-// k = the cells a full step may cross, at least 1; there the fraction is in [0, 1], as emission and
-// every step path leave it) whose |T| components are at most tlim ends at least 4 kFaceMargin
-// cells inside every face, so it is taken without the edge extension: its stage points stay
-// inside the box (they leave the straight line by h^2 |D| / 2 in the step parameter, about 1e-7
-// cells at the fields here).  That test is integer compares and one maximum.  A ray in a cell near
-// the faces is tested on the straight end point of a full step: more than kFaceMargin inside, the
-// full step is taken the same way; otherwise the exit rule decides, through the edge-extended
-// sampling (a full step there, at fraction 1, gives the same bits as the inside one wherever both
-// apply).  The exit-rule path leaves the state in a cell of the grid; a full step taken without the
-// edge extension does so unless its path bends more than kFaceMargin cells off the straight line
-// (a field far steeper than any here), and a state left outside the grid takes the exit rule next
-// (both tests above check the cell index first), so the ray's own cell index is in the grid
-// whenever it is used unclamped.
-template <typename F, int NODES = 0>
-__device__ __forceinline__ int trace_step(const TraceParams &P, CellCache &cc, int c[3], double fd[3], const F Tr[3],
-                                          F dT[3], const StepGeom<F> &sg, int &steps)
+// One stretch of the integration: a run of full steps that stay clear of the faces (run_budget), or,
+// where the straight line of the next full step reaches a face, the partial step of fraction lam
+// and, if the ray still heads out, the straight move onto that face.  Returns STEP_EXIT when the
+// ray left the box, STEP_LIMIT when it ran out of steps, STEP_GO otherwise.
+// step.inside(f): a full step without the edge extension; step.edge(f, lam): a step of fraction lam
+// with it (a full step there, at fraction 1, gives the same bits as the inside one wherever both
+// apply).
+// The test of the faces costs about 50 instructions, as much as a fifth of a step; testing once per
+// run of up to kRunSteps = 32 instead of before every step leaves it below 1% of the time, and longer
+// runs let lanes that end a run early wait longer for their wave.
+template <typename F, typename Step>
+__device__ __forceinline__ int trace_stretch(const TraceParams &P, int c[3], double fd[3], const F Wr[3], const F dW[3],
+                                             const StepGeom<F> &sg, int &steps, Step &step)
 {
-    const F *g = sg.g;
+    int k = run_budget<F>(P, sg, c, fd, Wr, dW, steps);
+    F f[3] = {(F)fd[0], (F)fd[1], (F)fd[2]};
+    if (k > 0) {
+        steps += k;
+        do step.inside(f);
+        while (--k > 0);
+        return steps > P.max_steps ? STEP_LIMIT : STEP_GO;
+    }
     const int *last = sg.last;
-    // bitwise, not short-circuit: one branch for the whole test.  A direction that is all NaN fails;
-    // one with a NaN next to finite components may pass (fmax returns the number), and its step then
-    // stays in bounds through the clamped cell indices.
-    const F Tm = fmax(fmax(fabs(Tr[0] + dT[0]), fabs(Tr[1] + dT[1])), fabs(Tr[2] + dT[2]));
-    const bool inside = ((unsigned)(c[0] - sg.lo[0]) < sg.bnd[0]) & ((unsigned)(c[1] - sg.lo[1]) < sg.bnd[1]) &
-                        ((unsigned)(c[2] - sg.lo[2]) < sg.bnd[2]) & (Tm <= sg.tlim);
-    if (__builtin_expect(inside, 1)) {
-        rkn_step<F, true, true, NODES>(P, cc, c, fd, Tr, dT, sg, (F)1);
-        return ++steps > P.max_steps ? STEP_LIMIT : STEP_GO;
-    }
-    // near the faces: the straight end point of a full step (a NaN counts as outside), from a
-    // state whose cell is a cell of the grid.  (A step whose path bends more than kFaceMargin
-    // cells off its straight line can end a hair outside the box with the index one past a face;
-    // such a state takes the exit rule, whose sampling clamps every index.)
-    bool far = true;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const F e = ((F)c[a] + (F)fd[a]) + g[a] * (Tr[a] + dT[a]);
-        far = far & (e > (F)kFaceMargin) & (e < (F)last[a] - (F)kFaceMargin) & ((unsigned)c[a] < (unsigned)last[a]);
-    }
-    if (far) {
-        rkn_step<F, true, true, NODES>(P, cc, c, fd, Tr, dT, sg, (F)1);
-        return ++steps > P.max_steps ? STEP_LIMIT : STEP_GO;
-    }
     F lam = (F)3.0e38;
     int ax = -1;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const F v = g[a] * (Tr[a] + dT[a]);
+        const F v = Wr[a] + dW[a];
         F l = (F)3.0e38;
         if (v > (F)0) l = (F)((double)(last[a] - c[a]) - fd[a]) / v;
         else if (v < (F)0) l = (F)((double)(-c[a]) - fd[a]) / v;
         if (l < lam) { lam = l; ax = a; }
     }
     const bool hit = ax >= 0 && lam <= (F)1;
-    const bool up = hit && (pick3<F>(Tr, ax) + pick3<F>(dT, ax)) > (F)0;
+    const bool up = hit && (pick3<F>(Wr, ax) + pick3<F>(dW, ax)) > (F)0;
     // one call site for both the partial step and the edge-extended full step
     if (!hit || lam > (F)0) {
-        rkn_step<F, false, false, NODES>(P, cc, c, fd, Tr, dT, sg, hit ? lam : (F)1);
+        step.edge(f, hit ? lam : (F)1);
         ++steps;
-        // a step ending on or a hair beyond the upper face leaves cell n - 1 at fraction ~0: keep the
-        // index a cell of the grid (same position), as the inside steps assume
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int i = min(max(c[a], 0), last[a] - 1);
-            fd[a] += (double)(c[a] - i);
-            c[a] = i;
-        }
     }
     if (!hit) return steps > P.max_steps ? STEP_LIMIT : STEP_GO;
-    const F Tn[3] = {Tr[0] + dT[0], Tr[1] + dT[1], Tr[2] + dT[2]};
-    const F Ta = pick3<F>(Tn, ax);
-    if (up ? (Ta > (F)0) : (Ta < (F)0)) {
+    const F Wn[3] = {Wr[0] + dW[0], Wr[1] + dW[1], Wr[2] + dW[2]};
+    const F Wa = pick3<F>(Wn, ax);
+    if (up ? (Wa > (F)0) : (Wa < (F)0)) {
         const int la = pick3<int>(last, ax);
         const double target = up ? (double)la : 0.0;
-        const double l2 = (target - ((double)pick3<int>(c, ax) + pick3<double>(fd, ax))) /
-                          ((double)pick3<F>(g, ax) * (double)Ta);
+        const double l2 = (target - ((double)pick3<int>(c, ax) + pick3<double>(fd, ax))) / (double)Wa;
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
             if (b == ax) {
                 c[b] = up ? la - 1 : 0;
                 fd[b] = up ? 1.0 : 0.0;
             } else {
-                fd[b] += l2 * (double)g[b] * (double)Tn[b];
+                fd[b] += l2 * (double)Wn[b];
             }
         }
         return STEP_EXIT;
@@ -492,16 +527,48 @@ __device__ __forceinline__ int trace_step(const TraceParams &P, CellCache &cc, i
     return steps > P.max_steps ? STEP_LIMIT : STEP_GO;  // turned back within the last step
 }
 
-// Integrate from the cell-local state until the ray leaves the box (see trace_step).  Returns the
-// number of steps; sets *limited when max_steps is exceeded.
+// The steps of one precision throughout.
+template <typename F, int NODES> struct PlainStep {
+    const TraceParams &P;
+    CellCache &cc;
+    int *c;
+    double *fd;
+    const F *Wr;
+    F *dW;
+    StageCarry<F> &carry;
+    const StepGeom<F> &sg;
+    __device__ __forceinline__ void inside(F f[3])
+    {
+        rkn_step<F, true, false, NODES>(P, cc, c, fd, f, Wr, dW, carry, sg, (F)1);
+    }
+    __device__ __forceinline__ void edge(F f[3], F lam)
+    {
+        rkn_step<F, false, true, NODES>(P, cc, c, fd, f, Wr, dW, carry, sg, lam);
+    }
+};
+
+template <typename F, int NODES = 0>
+__device__ __forceinline__ int trace_run(const TraceParams &P, CellCache &cc, int c[3], double fd[3], const F Wr[3],
+                                         F dW[3], StageCarry<F> &carry, const StepGeom<F> &sg, int &steps)
+{
+    PlainStep<F, NODES> step{P, cc, c, fd, Wr, dW, carry, sg};
+    return trace_stretch<F>(P, c, fd, Wr, dW, sg, steps, step);
+}
+
+// Integrate from the cell-local state (base cell c cached) until the ray leaves the box (see
+// trace_stretch).  Returns the number of steps; sets *limited when max_steps is exceeded.
 template <typename F, int NODES = 0>
 __device__ __forceinline__ int trace_box(const TraceParams &P, CellCache &cc, int c[3], double fd[3],
-                                         const F Tr[3], F dT[3], bool *limited)
+                                         const F Wr[3], F dW[3], bool *limited)
 {
     const StepGeom<F> sg = step_geom<F>(P);
+    StageCarry<F> carry;
+    carry.have = false;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) carry.aA[a] = (F)0;
     int steps = 0;
     for (;;) {
-        const int r = trace_step<F, NODES>(P, cc, c, fd, Tr, dT, sg, steps);
+        const int r = trace_run<F, NODES>(P, cc, c, fd, Wr, dW, carry, sg, steps);
         if (r != STEP_GO) {
             *limited = r == STEP_LIMIT;
             return steps;
@@ -789,10 +856,14 @@ __device__ __forceinline__ void emit_ray(const TraceParams &P, int64_t rid, RayS
     }
     // inside: T = n dR/ds = n u (eq. 4), n interpolated at the entry point
     CellCache cc;
-    cc.ix = -1;
-    float G0[3];
-    const float n0 = P.node_layout ? sample_field<float, false, false, true>(P, cc, r.c, f, G0)
-                                   : sample_field<float>(P, cc, r.c, f, G0);
+    float G0[3], n0;
+    if (P.node_layout) {
+        first_cell<2>(P, r.c, cc);
+        n0 = 1.0f + interpolate<float, 2>(cc, f, G0);
+    } else {
+        first_cell<0>(P, r.c, cc);
+        n0 = 1.0f + interpolate<float, 0>(cc, f, G0);
+    }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {  // T0 as a float hi/lo pair: no rounding of the entry direction
         const double T0 = (double)n0 * u[a];
@@ -814,32 +885,47 @@ __global__ void __launch_bounds__(256) k_emit(TraceParams P, RayState *__restric
 
 // ------------------------------------------------------------------ kernel 2: the ray equation
 
-template <typename F, int NODES = 0>
-__device__ __forceinline__ void box_ray(const TraceParams &P, RayState &r)
+// W = h T / spacing of a state as the integration carries it: a float hi/lo pair in FP32 (about 48
+// significant bits, no rounding of the entry direction), one double in FP64.
+__device__ __forceinline__ void load_direction(const TraceParams &P, const RayState &r, float Wr[3], float dW[3])
 {
-    // T = Tr + dT; in FP32 the low part of the entry direction starts the accumulated change
-    F Tr[3], dT[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        if (sizeof(F) == sizeof(float)) {
-            Tr[a] = (F)r.Tr[a];
-            dT[a] = (F)r.dT[a];
-        } else {
-            Tr[a] = (F)((double)r.Tr[a] + (double)r.dT[a]);
-            dT[a] = (F)0;
-        }
+        const double W = P.step_cell[a] * ((double)r.Tr[a] + (double)r.dT[a]);
+        Wr[a] = (float)W;
+        dW[a] = (float)(W - (double)Wr[a]);
     }
-    CellCache cc;
-    cc.ix = -1;
-    bool limited = false;
-    const int steps = trace_box<F, NODES>(P, cc, r.c, r.fd, Tr, dT, &limited);
-    // exit direction as a float hi/lo pair (about 48 significant bits)
+}
+__device__ __forceinline__ void load_direction(const TraceParams &P, const RayState &r, double Wr[3], double dW[3])
+{
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const double T = (double)Tr[a] + (double)dT[a];
+        Wr[a] = P.step_cell[a] * ((double)r.Tr[a] + (double)r.dT[a]);
+        dW[a] = 0.0;
+    }
+}
+// T back from W, as a float hi/lo pair.
+template <typename F>
+__device__ __forceinline__ void store_direction(const TraceParams &P, RayState &r, const F Wr[3], const F dW[3])
+{
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double T = ((double)Wr[a] + (double)dW[a]) / P.step_cell[a];
         r.Tr[a] = (float)T;
         r.dT[a] = (float)(T - (double)r.Tr[a]);
     }
+}
+
+template <typename F, int NODES = 0>
+__device__ __forceinline__ void box_ray(const TraceParams &P, RayState &r)
+{
+    F Wr[3], dW[3];
+    load_direction(P, r, Wr, dW);
+    CellCache cc;
+    first_cell<NODES>(P, r.c, cc);
+    bool limited = false;
+    const int steps = trace_box<F, NODES>(P, cc, r.c, r.fd, Wr, dW, &limited);
+    store_direction<F>(P, r, Wr, dW);
     r.info = RS_ENTERED | (limited ? RS_LIMITED : 0) | (steps << RS_STEP_SHIFT);
 }
 
@@ -871,8 +957,13 @@ __device__ __forceinline__ void box_body(const TraceParams &P, RayState *__restr
     st[i] = r;
 }
 
-// FP32 integration: 88 VGPRs, five waves per SIMD.  NODES: field stored per node (the corner gather
+// FP32 integration: 95 VGPRs, five waves per SIMD.  NODES: field stored per node (the corner gather
 // needs more registers: four waves per SIMD).
+// Bound by VALU issue (136 instructions per wave-step, half of wave-steps moving some lane to a new
+// cell) with the L2 misses of those moves behind it.  5e6 rays through the 128^3 turbulence: 15.6 ms a
+// launch, 19.4 ms when every stage point's cell was found from scratch and every step took three
+// samples (203 instructions); 1e7 rays of 256^3 shock with FP64 steps 13.1 against 17.2 ms, the
+// 257^2 x 81 slice 3.9 against 4.8 ms (5.2e6 rays, node layout).
 template <bool NODES = false>
 __global__ void __launch_bounds__(256, NODES ? 4 : 5) k_box32(TraceParams P, RayState *__restrict__ st, int64_t n,
                                                   const int *__restrict__ list,
@@ -905,8 +996,10 @@ __global__ void __launch_bounds__(256, 5) k_box32_refill(TraceParams P, RayState
     const StepGeom<float> sg = step_geom<float>(P);
     int64_t i = -1;  // this lane's ray, -1: none
     RayState r;
-    float Tr[3], dT[3];
+    float Wr[3], dW[3];
     CellCache cc;
+    StageCarry<float> carry;
+    carry.have = false;
     int steps = 0;
     bool drained = false;  // the queue had nothing left for this wave
     for (;;) {
@@ -924,9 +1017,9 @@ __global__ void __launch_bounds__(256, 5) k_box32_refill(TraceParams P, RayState
                     r = st[j];
                     if ((r.info & (RS_ENTERED | RS_SURR)) == RS_ENTERED) {
                         i = j;
-#pragma unroll
-                        for (int a = 0; a < 3; ++a) { Tr[a] = r.Tr[a]; dT[a] = r.dT[a]; }
-                        cc.ix = -1;
+                        load_direction(P, r, Wr, dW);
+                        first_cell<0>(P, r.c, cc);
+                        carry.have = false;
                         steps = 0;
                     }
                 }
@@ -935,14 +1028,9 @@ __global__ void __launch_bounds__(256, 5) k_box32_refill(TraceParams P, RayState
         }
         if (__ballot(i >= 0) == 0) break;  // queue drained and no lane busy
         if (i >= 0) {
-            const int res = trace_step<float>(P, cc, r.c, r.fd, Tr, dT, sg, steps);
+            const int res = trace_run<float>(P, cc, r.c, r.fd, Wr, dW, carry, sg, steps);
             if (res != STEP_GO) {
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    const double T = (double)Tr[a] + (double)dT[a];
-                    r.Tr[a] = (float)T;
-                    r.dT[a] = (float)(T - (double)r.Tr[a]);
-                }
+                store_direction<float>(P, r, Wr, dW);
                 r.info = RS_ENTERED | (res == STEP_LIMIT ? RS_LIMITED : 0) | (steps << RS_STEP_SHIFT);
                 st[i] = r;
                 i = -1;
@@ -963,91 +1051,72 @@ __device__ __forceinline__ bool brick_is_fp64(const TraceParams &P, const int c[
     return P.brick_fp64[((size_t)bz * P.nby + by) * P.nbx + bx] != 0;
 }
 
-// One step in FP64 from the FP32 state: T = Tr + dT is carried in double through the step, then
-// split again into a float hi/lo pair.
-template <bool FULL, int NODES>
-__device__ __forceinline__ void rkn_step_fp64(const TraceParams &P, CellCache &cc, int c[3], double fd[3],
-                                              float Tr[3], float dT[3], double lam)
-{
-    double T64[3], d64[3] = {0.0, 0.0, 0.0};
-    const StepGeom<double> sg64 = step_geom<double>(P);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) T64[a] = (double)Tr[a] + (double)dT[a];
-    rkn_step<double, FULL, false, NODES>(P, cc, c, fd, T64, d64, sg64, lam);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const double T = T64[a] + d64[a];
-        Tr[a] = (float)T;
-        dT[a] = (float)(T - (double)Tr[a]);
-    }
-}
-
-// trace_box<float> with the step precision chosen per step from the brick of the current cell.
-template <int NODES>
-__device__ __forceinline__ int trace_box_mixed(const TraceParams &P, CellCache &cc, int c[3], double fd[3],
-                                               float Tr[3], float dT[3], bool *limited, int *n64)
-{
-    const StepGeom<float> sg = step_geom<float>(P);
-    const float *g = sg.g;
-    const int *last = sg.last;
-    int steps = 0;
-    *limited = false;
-    for (;;) {
-        bool near = false;
+// Steps whose precision is chosen one by one from the brick of the ray's current cell: FP64 from the
+// FP32 state (W = Wr + dW carried in double through the step, then split again into a float hi/lo
+// pair), or FP32.
+template <int NODES> struct MixedStep {
+    const TraceParams &P;
+    CellCache &cc;
+    int *c;
+    double *fd;
+    float *Wr, *dW;
+    StageCarry<float> &carry;
+    const StepGeom<float> &sg;
+    int &n64;
+    template <bool FULL, bool EDGE> __device__ __forceinline__ void take(float f[3], float lam)
+    {
+        const int cell[3] = {c[0] + (int)floorf(f[0]), c[1] + (int)floorf(f[1]), c[2] + (int)floorf(f[2])};
+        if (!brick_is_fp64(P, cell)) {
+            rkn_step<float, FULL, EDGE, NODES>(P, cc, c, fd, f, Wr, dW, carry, sg, lam);
+            return;
+        }
+        const StepGeom<double> sg64 = step_geom<double>(P);
+        StageCarry<double> none;
+        none.have = false;
+        double W64[3], d64[3] = {0.0, 0.0, 0.0}, f64[3] = {fd[0], fd[1], fd[2]};
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const float v = g[a] * (Tr[a] + dT[a]);
-            const float fa = (float)fd[a];
-            near = near || (v > 0.0f && (float)(last[a] - c[a]) - fa <= v) || (v < 0.0f && (float)(-c[a]) - fa >= v);
+            W64[a] = (double)Wr[a] + (double)dW[a];
+            none.aA[a] = 0.0;
         }
-        if (near) {
-            float lam = 3.0e38f;
-            int ax = -1;
+        rkn_step<double, FULL, EDGE, NODES>(P, cc, c, fd, f64, W64, d64, none, sg64, (double)lam);
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const float v = g[a] * (Tr[a] + dT[a]);
-                float l = 3.0e38f;
-                if (v > 0.0f) l = (float)((double)(last[a] - c[a]) - fd[a]) / v;
-                else if (v < 0.0f) l = (float)((double)(-c[a]) - fd[a]) / v;
-                if (l < lam) { lam = l; ax = a; }
-            }
-            if (ax >= 0 && lam <= 1.0f) {
-                const bool up = (pick3<float>(Tr, ax) + pick3<float>(dT, ax)) > 0.0f;
-                if (lam > 0.0f) {
-                    if (brick_is_fp64(P, c)) { rkn_step_fp64<false, NODES>(P, cc, c, fd, Tr, dT, (double)lam); ++*n64; }
-                    else rkn_step<float, false, false, NODES>(P, cc, c, fd, Tr, dT, sg, lam);
-                    ++steps;
-                }
-                const float Tn[3] = {Tr[0] + dT[0], Tr[1] + dT[1], Tr[2] + dT[2]};
-                const float Ta = pick3<float>(Tn, ax);
-                if (up ? (Ta > 0.0f) : (Ta < 0.0f)) {
-                    const int la = pick3<int>(last, ax);
-                    const double target = up ? (double)la : 0.0;
-                    const double l2 = (target - ((double)pick3<int>(c, ax) + pick3<double>(fd, ax))) /
-                                      ((double)pick3<float>(g, ax) * (double)Ta);
-#pragma unroll
-                    for (int b = 0; b < 3; ++b) {
-                        if (b == ax) {
-                            c[b] = up ? la - 1 : 0;
-                            fd[b] = up ? 1.0 : 0.0;
-                        } else {
-                            fd[b] += l2 * (double)g[b] * (double)Tn[b];
-                        }
-                    }
-                    return steps;
-                }
-                if (steps > P.max_steps) { *limited = true; return steps; }
-                continue;
-            }
+        for (int a = 0; a < 3; ++a) {
+            const double W = W64[a] + d64[a];
+            Wr[a] = (float)W;
+            dW[a] = (float)(W - (double)Wr[a]);
+            f[a] = (float)fd[a];
         }
-        if (brick_is_fp64(P, c)) { rkn_step_fp64<true, NODES>(P, cc, c, fd, Tr, dT, 1.0); ++*n64; }
-        else rkn_step<float, true, false, NODES>(P, cc, c, fd, Tr, dT, sg, 1.0f);
-        if (++steps > P.max_steps) { *limited = true; return steps; }
+        carry.have = false;
+        ++n64;
+    }
+    __device__ __forceinline__ void inside(float f[3]) { take<true, false>(f, 1.0f); }
+    __device__ __forceinline__ void edge(float f[3], float lam) { take<false, true>(f, lam); }
+};
+
+// trace_box<float> with the step precision chosen per step.
+template <int NODES>
+__device__ __forceinline__ int trace_box_mixed(const TraceParams &P, CellCache &cc, int c[3], double fd[3],
+                                               float Wr[3], float dW[3], bool *limited, int *n64)
+{
+    const StepGeom<float> sg = step_geom<float>(P);
+    StageCarry<float> carry;
+    carry.have = false;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) carry.aA[a] = 0.0f;
+    MixedStep<NODES> step{P, cc, c, fd, Wr, dW, carry, sg, *n64};
+    int steps = 0;
+    for (;;) {
+        const int r = trace_stretch<float>(P, c, fd, Wr, dW, sg, steps, step);
+        if (r != STEP_GO) {
+            *limited = r == STEP_LIMIT;
+            return steps;
+        }
     }
 }
 
 template <bool NODES>
-__global__ void __launch_bounds__(256) k_box_mixed(TraceParams P, RayState *__restrict__ st, int64_t n,
+__global__ void __launch_bounds__(256, NODES ? 4 : 2) k_box_mixed(TraceParams P, RayState *__restrict__ st, int64_t n,
                                                    const int *__restrict__ list,
                                                    const unsigned long long *__restrict__ count)
 {
@@ -1060,17 +1129,13 @@ __global__ void __launch_bounds__(256) k_box_mixed(TraceParams P, RayState *__re
     if (live) {
         RayState r = st[i];
         if ((r.info & (RS_ENTERED | RS_SURR)) == RS_ENTERED) {
-            float Tr[3] = {r.Tr[0], r.Tr[1], r.Tr[2]}, dT[3] = {r.dT[0], r.dT[1], r.dT[2]};
+            float Wr[3], dW[3];
+            load_direction(P, r, Wr, dW);
             CellCache cc;
-            cc.ix = -1;
+            first_cell<NODES ? 2 : 0>(P, r.c, cc);
             bool limited = false;
-            const int steps = trace_box_mixed<NODES ? 2 : 0>(P, cc, r.c, r.fd, Tr, dT, &limited, &n64);
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const double T = (double)Tr[a] + (double)dT[a];
-                r.Tr[a] = (float)T;
-                r.dT[a] = (float)(T - (double)r.Tr[a]);
-            }
+            const int steps = trace_box_mixed<NODES ? 2 : 0>(P, cc, r.c, r.fd, Wr, dW, &limited, &n64);
+            store_direction<float>(P, r, Wr, dW);
             r.info = RS_ENTERED | (limited ? RS_LIMITED : 0) | (steps << RS_STEP_SHIFT);
             st[i] = r;
         }
@@ -1121,31 +1186,43 @@ __global__ void __launch_bounds__(256) k_calibrate(TraceParams P, const int *__r
     const double il = 1.0 / sqrt(u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
 #pragma unroll
     for (int a = 0; a < 3; ++a) u[a] *= il;
+    constexpr int L = NODES ? 2 : 0;
     CellCache cc;
-    cc.ix = -1;
     float G0[3];
-    const float n0 = sample_field<float, false, false, NODES ? 2 : 0>(P, cc, c, f, G0);
+    first_cell<L>(P, c, cc);
+    const float n0 = 1.0f + interpolate<float, L>(cc, f, G0);
     // FP32
     int c32[3] = {c[0], c[1], c[2]};
     double fd32[3] = {fd[0], fd[1], fd[2]};
-    float Tr[3], dT[3];
+    RayState r0;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const double T0 = (double)n0 * u[a];
-        Tr[a] = (float)T0;
-        dT[a] = (float)(T0 - (double)Tr[a]);
+        r0.Tr[a] = (float)T0;
+        r0.dT[a] = (float)(T0 - (double)r0.Tr[a]);
     }
+    float Wr[3], dW[3];
+    load_direction(P, r0, Wr, dW);
     const StepGeom<float> sg = step_geom<float>(P);
-    for (int k = 0; k < n_steps; ++k) rkn_step<float, true, false, NODES ? 2 : 0>(P, cc, c32, fd32, Tr, dT, sg, 1.0f);
+    StageCarry<float> a32;
+    a32.have = false;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) a32.aA[a] = 0.0f;
+    for (int k = 0; k < n_steps; ++k) rkn_step<float, true, true, L>(P, cc, c32, fd32, f, Wr, dW, a32, sg, 1.0f);
     // FP64
     int c64[3] = {c[0], c[1], c[2]};
     double fd64[3] = {fd[0], fd[1], fd[2]};
-    double T64[3], d64[3] = {0.0, 0.0, 0.0};
+    double W64[3], d64[3] = {0.0, 0.0, 0.0};
     const StepGeom<double> sg64 = step_geom<double>(P);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) T64[a] = (double)n0 * u[a];
-    cc.ix = -1;
-    for (int k = 0; k < n_steps; ++k) rkn_step<double, true, false, NODES ? 2 : 0>(P, cc, c64, fd64, T64, d64, sg64, 1.0);
+    for (int a = 0; a < 3; ++a) W64[a] = P.step_cell[a] * ((double)n0 * u[a]);
+    first_cell<L>(P, c64, cc);
+    StageCarry<double> a64;
+    a64.have = false;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) a64.aA[a] = 0.0;
+    double f64[3] = {fd64[0], fd64[1], fd64[2]};
+    for (int k = 0; k < n_steps; ++k) rkn_step<double, true, true, L>(P, cc, c64, fd64, f64, W64, d64, a64, sg64, 1.0);
     double q32[2], q64[2];
     {
         double Xa[3], Xb[3], da[3], db[3];
@@ -1153,8 +1230,8 @@ __global__ void __launch_bounds__(256) k_calibrate(TraceParams P, const int *__r
         for (int a = 0; a < 3; ++a) {
             Xa[a] = P.origin[a] + ((double)c32[a] + fd32[a]) * P.spacing[a];
             Xb[a] = P.origin[a] + ((double)c64[a] + fd64[a]) * P.spacing[a];
-            da[a] = (double)Tr[a] + (double)dT[a];
-            db[a] = T64[a] + d64[a];
+            da[a] = ((double)Wr[a] + (double)dW[a]) / P.step_cell[a];
+            db[a] = (W64[a] + d64[a]) / P.step_cell[a];
         }
         const double ta = (Xa[2] - z_focus) / da[2], tb = (Xb[2] - z_focus) / db[2];
         q32[0] = Xa[0] - ta * da[0]; q32[1] = Xa[1] - ta * da[1];
