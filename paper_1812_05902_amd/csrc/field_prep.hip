@@ -97,6 +97,43 @@ k_field_prep(const float *__restrict__ rho, float4 *__restrict__ cells, unsigned
         out[m] = make_float4((float)c[m][0], (float)c[m][1], (float)c[m][2], (float)c[m][3]);
 }
 
+// One axis of the distance map: the least over r of max(r, distance so far at r bricks along the axis
+// on either side).  Taken along x, then y, then z from 0 / kSkipMax this gives the largest-axis
+// distance to the nearest marked brick.  FIRST reads the gradients themselves; WORDS: from the bytes of
+// tmp into the words of gmax, otherwise from the words into the bytes.  A few thousand to a few hundred
+// thousand bricks: launch-bound.
+template <bool FIRST, bool WORDS>
+__global__ void __launch_bounds__(256) k_skip_pass(unsigned *__restrict__ gmax, unsigned char *__restrict__ tmp, int64_t n,
+                                                   int64_t stride, int len)
+{
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= n) return;
+    const int i = (int)((q / stride) % len);
+    auto at = [&](int64_t k) {
+        if (WORDS) return (int)tmp[k];
+        const unsigned v = gmax[k];
+        return FIRST ? (v ? 0 : kSkipMax) : skip_distance(v);
+    };
+    int best = at(q);
+    for (int r = 1; r < best; ++r) {
+        if (i - r < 0 && i + r >= len) break;
+        if (i - r >= 0) best = min(best, max(r, at(q - r * stride)));
+        if (i + r < len) best = min(best, max(r, at(q + r * stride)));
+    }
+    if (!WORDS) tmp[q] = (unsigned char)best;
+    else if (best) gmax[q] = kSkipBit | (unsigned)best;
+}
+
+// The distances of the last pass back into gmax, and tmp zero again.
+__global__ void __launch_bounds__(256) k_skip_finish(unsigned *__restrict__ gmax, unsigned char *__restrict__ tmp,
+                                                     int64_t n)
+{
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= n) return;
+    if (tmp[q]) gmax[q] = kSkipBit | (unsigned)tmp[q];
+    tmp[q] = 0;
+}
+
 // Fingerprint of a field: sum over its 32-bit words w_k of SplitMix64's finaliser applied to
 // (k << 32 | w_k), wrapping mod 2^64 (integer atomics: independent of the order of the blocks).
 __global__ void __launch_bounds__(256) k_checksum(const unsigned *__restrict__ w, int64_t n,
@@ -182,6 +219,17 @@ int launch_field_prep(const float *rho, float4 *cells, unsigned *brick_gmax, int
         hipLaunchKernelGGL(k_field_nodes, ngrid, block, 0, stream, rho, cells, nx, ny, nz, K / spacing[0],
                            K / spacing[1], K / spacing[2], K);
     }
+    return (int)hipGetLastError();
+}
+
+int launch_skip_map(unsigned *gmax, unsigned char *tmp, int nbx, int nby, int nbz, hipStream_t stream)
+{
+    const int64_t n = (int64_t)nbx * nby * nbz;
+    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    hipLaunchKernelGGL((k_skip_pass<true, false>), grid, block, 0, stream, gmax, tmp, n, (int64_t)1, nbx);
+    hipLaunchKernelGGL((k_skip_pass<false, true>), grid, block, 0, stream, gmax, tmp, n, (int64_t)nbx, nby);
+    hipLaunchKernelGGL((k_skip_pass<false, false>), grid, block, 0, stream, gmax, tmp, n, (int64_t)nbx * nby, nbz);
+    hipLaunchKernelGGL(k_skip_finish, grid, block, 0, stream, gmax, tmp, n);
     return (int)hipGetLastError();
 }
 

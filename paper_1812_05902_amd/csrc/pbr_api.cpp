@@ -115,6 +115,7 @@ void fill_params(const pbr_ctx *ctx, const Derived &d, double ds, TraceParams *o
     std::memset(&P, 0, sizeof P);
     P.cells = ctx->cells;
     P.brick_fp64 = ctx->brick_fp64;
+    P.skip = ctx->brick_gmax;
     P.nbx = ctx->layout.nbx; P.nby = ctx->layout.nby; P.nbz = ctx->layout.nbz;
     P.nx = ctx->nx; P.ny = ctx->ny; P.nz = ctx->nz;
     P.max_steps = max_steps_for(ctx, ds);
@@ -375,12 +376,15 @@ int set_field(pbr_ctx *ctx, const float *rho_dev, int nx, int ny, int nz, const 
         if (e) return hip_fail(ctx, e, "clear brick tables");
         e = pbr::launch_field_prep(rho_dev, (float4 *)(base + L.cells_off), (unsigned *)(base + L.gmax_off),
                                    nx, ny, nz, spacing, K, ctx->stream, nodes);
+        if (!e) e = pbr::launch_skip_map((unsigned *)(base + L.gmax_off), (unsigned char *)(base + L.flags_off), L.nbx,
+                                         L.nby, L.nbz, ctx->stream);
         if (e) return hip_fail(ctx, e, "field preparation launch");
     }
     ctx->layout = L;
     ctx->brick_gmax = (unsigned *)(base + L.gmax_off);
     ctx->brick_fp64 = (unsigned char *)(base + L.flags_off);
     ctx->n_fp64_bricks = 0;
+    ctx->flags_written = false;
     ctx->cells = (const float4 *)(base + L.cells_off);
     ctx->nx = nx; ctx->ny = ny; ctx->nz = nz;
     for (int a = 0; a < 3; ++a) { ctx->origin[a] = origin[a]; ctx->spacing[a] = spacing[a]; }
@@ -630,6 +634,8 @@ int emit_and_trace_impl(pbr_ctx *ctx, const float *src_dev, int64_t n_src, int32
     const int prec = (flags & PBR_PREC_FP64_ALL) ? pbr::PREC_FP64
                      : ((flags & PBR_PREC_SHOCK_FP64) && ctx->n_fp64_bricks > 0) ? pbr::PREC_MIXED
                      : pbr::PREC_FP32;
+    // flags of the caller's own may ask for FP64 steps in gas without a gradient: count and take them
+    if (prec == pbr::PREC_MIXED && ctx->flags_written) P.skip = nullptr;
     const int64_t n_chunks = (P.n_rays + ray_chunk - 1) / ray_chunk;
     // per-launch timing events (created on demand, so not in the allocation-free variant)
     const bool launch_ev = stats && !noalloc;
@@ -772,6 +778,7 @@ int pbr_calibrate_precision(pbr_ctx *ctx, double tol_px, double steep_frac, int3
     if (!e) e = (int)hipStreamSynchronize(ctx->stream);
     if (e) return hip_fail(ctx, e, "write brick flags");
     ctx->n_fp64_bricks = nf;
+    ctx->flags_written = false;
     if (out) {
         out->n_bricks = nb;
         out->n_steep = ns;
@@ -805,6 +812,7 @@ int pbr_brick_flags(pbr_ctx *ctx, uint8_t *inout_host, int64_t n_bricks, int wri
         if (!e) e = (int)hipStreamSynchronize(ctx->stream);
         if (e) return hip_fail(ctx, e, "write brick flags");
         ctx->n_fp64_bricks = nf;
+        ctx->flags_written = true;
     } else {
         e = (int)hipMemcpyAsync(inout_host, ctx->brick_fp64, (size_t)n_bricks, hipMemcpyDeviceToHost, ctx->stream);
         if (!e) e = (int)hipStreamSynchronize(ctx->stream);

@@ -25,10 +25,11 @@ struct pbr_ctx {
     int64_t src_sums_cap = 0;
     const int64_t *src_order = nullptr;     // processing order of the sources (PBR_SOURCE_ORDER), device
     int64_t src_order_n = 0;
-    unsigned *brick_gmax = nullptr;        // per-brick max |grad n| (float bits), device
+    unsigned *brick_gmax = nullptr;        // per-brick max |grad n| (float bits) or distance to one, device
     unsigned char *brick_fp64 = nullptr;   // per-brick FP64 flags, device
     pbr::FieldLayout layout{};
     int64_t n_fp64_bricks = 0;
+    bool flags_written = false;            // the FP64 flags are the caller's (pbr_brick_flags), not the calibration's
     int nx = 0, ny = 0, nz = 0;
     double origin[3] = {0, 0, 0}, spacing[3] = {0, 0, 0};
     double K = 0.0, rho_inf = 0.0;

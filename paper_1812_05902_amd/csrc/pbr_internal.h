@@ -42,7 +42,8 @@ constexpr int kCellFloat4 = 8;
 constexpr int kBrick = 8;
 
 // Byte layout of the field workspace: cell records, then per-brick max |grad n| (uint32 float
-// bits), then per-brick FP64 flags (uint8); each part 256-byte aligned.
+// bits; for a brick without any gradient its distance to one that has some, see launch_skip_map), then
+// per-brick FP64 flags (uint8); each part 256-byte aligned.
 // nodes = 0: per-cell records (128 B per cell); nodes = 1: per-node float4 (n - 1, grad n), 16 B per
 // node, from which a gather forms the same coefficients (8x less memory for fine grids).
 struct FieldLayout {
@@ -72,6 +73,7 @@ inline FieldLayout field_layout(int nx, int ny, int nz, bool nodes = false)
 struct TraceParams {
     const float4 *cells;   // field records (see above)
     const unsigned char *brick_fp64;  // per-brick FP64 flags (mixed precision)
+    const unsigned *skip;             // per-brick distance to the nearest gradient (skip_distance; null: step through)
     int nbx, nby, nbz;     // brick counts
     int nx, ny, nz;        // node counts
     int max_steps;
@@ -244,6 +246,13 @@ struct BatchConfig {
 // Writes the cell records and (atomically) the per-brick max |grad n|; gmax must be zeroed.
 int launch_field_prep(const float *rho, float4 *cells, unsigned *brick_gmax, int nx, int ny, int nz,
                       const double spacing[3], double K, hipStream_t stream, bool nodes = false);
+// Replaces the zeros of gmax by kSkipBit | distance in bricks (largest axis distance, at most kSkipMax)
+// to the nearest brick whose gmax is not zero (as a float such a word is not above 0, like the zero it
+// replaces).  tmp: scratch, a byte per brick, left zero.
+constexpr unsigned kSkipBit = 0x80000000u;
+constexpr int kSkipMax = 127;
+int launch_skip_map(unsigned *gmax, unsigned char *tmp, int nbx, int nby, int nbz, hipStream_t stream);
+__host__ __device__ inline int skip_distance(unsigned word) { return (word & kSkipBit) ? (int)(word & 0xFFu) : 0; }
 // Precision calibration: for each listed brick, rays_per_brick sample rays integrated over
 // n_steps full steps in FP32 and in FP64 from the same state; err[k] = largest difference of
 // the image point (apparent source on the plane z_focus, times |M| / pitch) in pixels.

@@ -343,11 +343,19 @@ template <typename F> __device__ __forceinline__ StepGeom<F> step_geom(const Tra
     return sg;
 }
 
+// Steps before a ray whose last sample was zero looks for uniform gas (skip_uniform) again: a brick's
+// worth after a look that moved it, twice as many after each look in vain (gas that is uniform only
+// to the rounding of its density has zero samples everywhere and nothing to skip).
+constexpr int kLookSteps = 4;
+
 // The acceleration at the end point of the step before, when that step's last sample serves for it
 // (see rkn_step).
+// aA is a_C of the step before in any case (zero before the first step); cached: the base cell's
+// record is loaded; look: steps until a ray whose last sample was zero looks for uniform gas again.
 template <typename F> struct StageCarry {
-    F aA[3];
-    bool have;
+    F aA[3] = {(F)0, (F)0, (F)0};
+    bool have = false, cached = false;
+    int look = kLookSteps;
 };
 
 // Largest difference (cells) between the last stage point of a step and its end point for which the
@@ -414,11 +422,9 @@ __device__ __forceinline__ void rkn_step(const TraceParams &P, CellCache &cc, in
         f[a] = (F)fd[a];
         dW[a] = dW[a] + (FULL ? sixth : sixth * lam) * (aA[a] + sum[a]);
     }
-    if (sizeof(F) == sizeof(float)) {
-        carry.have = e <= (F)(6.0f * kReuse);
+    carry.have = sizeof(F) == sizeof(float) && e <= (F)(6.0f * kReuse);
 #pragma unroll
-        for (int a = 0; a < 3; ++a) carry.aA[a] = aA[a];
-    }
+    for (int a = 0; a < 3; ++a) carry.aA[a] = aA[a];
 }
 
 template <typename T> __device__ __forceinline__ T pick3(const T v[3], int k)
@@ -466,6 +472,68 @@ __device__ __forceinline__ int run_budget(const TraceParams &P, const StepGeom<F
 // loops: no dynamically indexed arrays.)
 enum : int { STEP_GO = 0, STEP_EXIT = 1, STEP_LIMIT = 2 };
 
+// Ray in gas of uniform index.  P.skip holds per brick (kBrick^3 cells) how many bricks away, in the
+// largest of the three axis distances, the nearest brick with a non-zero gradient at any of its nodes
+// lies.  Within such a cube of bricks D is exactly zero at every sample and the steps are straight
+// and equal, so all that end inside the cube are taken at once, and if the cube reaches the box face
+// that the ray heads for, the partial step and the move onto the face too: the same number of steps,
+// the same line, without the rounding of each step's increment.  Called where the last sample of the
+// ray was zero (or none has been taken).  Returns STEP_EXIT when the ray left the box.
+// Regions of ambient gas around a flow, the reference render of a BOS pair and the whole volume on
+// either side of a shock are of this kind: the 512^3 shock image (2e8 rays) took 21.7 ms per 1.7e7
+// rays stepping through them (98% of its steps).
+template <typename F>
+__device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], double fd[3], const F Wr[3], const F dW[3],
+                                            StageCarry<F> &carry, const int last[3], int &steps)
+{
+    const double W[3] = {(double)Wr[0] + (double)dW[0], (double)Wr[1] + (double)dW[1], (double)Wr[2] + (double)dW[2]};
+    if (!(fabs(W[0]) + fabs(W[1]) + fabs(W[2]) < 1.0e6)) return STEP_GO;
+    for (;;) {
+        int b[3];
+        double p[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            p[a] = (double)c[a] + fd[a];
+            b[a] = min(max((int)floor(p[a]), 0), last[a] - 1) / kBrick;
+        }
+        if (PBR_CHECKED && !access_ok(P, b[0] < P.nbx && b[1] < P.nby && b[2] < P.nbz)) return STEP_GO;
+        const int d = skip_distance(P.skip[((size_t)b[2] * P.nby + b[1]) * P.nbx + b[0]]);
+        if (d == 0) return STEP_GO;
+        double s = 3.0e38, end = 0.0;
+        int ax = -1;
+        bool face = false;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            if (W[a] == 0.0) continue;
+            const bool u = W[a] > 0.0;
+            const int e = u ? min((b[a] + d) * kBrick, last[a]) : max((b[a] - d + 1) * kBrick, 0);
+            const double l = fmax(((double)e - p[a]) / W[a], 0.0);
+            if (l < s) {
+                s = l;
+                ax = a;
+                end = (double)e;
+                face = e == (u ? last[a] : 0);
+            }
+        }
+        if (ax < 0 || !(s < (double)(P.max_steps - steps))) return STEP_GO;
+        // full steps while a whole one stays inside; at a face also the partial step onto it
+        const int m = face ? (int)ceil(s) : (int)floor(s * (1.0 - 1.0e-12));
+        if (!face && m < 1) return STEP_GO;
+        steps += m;
+        const double l = face ? s : (double)m;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const double q = face && a == ax ? end : p[a] + l * W[a];
+            c[a] = min(max((int)floor(q), 0), last[a] - 1);
+            fd[a] = q - (double)c[a];
+        }
+        carry.cached = false;
+        if (face) {
+            return STEP_EXIT;
+        }
+    }
+}
+
 // One stretch of the integration: a run of full steps that stay clear of the faces (run_budget), or,
 // where the straight line of the next full step reaches a face, the partial step of fraction lam
 // and, if the ray still heads out, the straight move onto that face.  Returns STEP_EXIT when the
@@ -476,11 +544,23 @@ enum : int { STEP_GO = 0, STEP_EXIT = 1, STEP_LIMIT = 2 };
 // The test of the faces costs about 50 instructions, as much as a fifth of a step; testing once per
 // run of up to kRunSteps = 32 instead of before every step leaves it below 1% of the time, and longer
 // runs let lanes that end a run early wait longer for their wave.
-template <typename F, typename Step>
-__device__ __forceinline__ int trace_stretch(const TraceParams &P, int c[3], double fd[3], const F Wr[3], const F dW[3],
-                                             const StepGeom<F> &sg, int &steps, Step &step)
+template <typename F, int NODES, typename Step>
+__device__ __forceinline__ int trace_stretch(const TraceParams &P, CellCache &cc, int c[3], double fd[3], const F Wr[3],
+                                             const F dW[3], StageCarry<F> &carry, const StepGeom<F> &sg, int &steps,
+                                             Step &step)
 {
+    const bool calm = (carry.aA[0] == (F)0) & (carry.aA[1] == (F)0) & (carry.aA[2] == (F)0);
+    if (calm && P.skip) {
+        const int before = steps;
+        if (skip_uniform<F>(P, c, fd, Wr, dW, carry, sg.last, steps) == STEP_EXIT) return STEP_EXIT;
+        carry.look = steps > before ? kLookSteps : min(2 * carry.look, kRunSteps);
+    }
+    if (!carry.cached) {
+        first_cell<NODES>(P, c, cc);
+        carry.cached = true;
+    }
     int k = run_budget<F>(P, sg, c, fd, Wr, dW, steps);
+    if (calm) k = min(k, carry.look);
     F f[3] = {(F)fd[0], (F)fd[1], (F)fd[2]};
     if (k > 0) {
         steps += k;
@@ -552,10 +632,10 @@ __device__ __forceinline__ int trace_run(const TraceParams &P, CellCache &cc, in
                                          F dW[3], StageCarry<F> &carry, const StepGeom<F> &sg, int &steps)
 {
     PlainStep<F, NODES> step{P, cc, c, fd, Wr, dW, carry, sg};
-    return trace_stretch<F>(P, c, fd, Wr, dW, sg, steps, step);
+    return trace_stretch<F, NODES>(P, cc, c, fd, Wr, dW, carry, sg, steps, step);
 }
 
-// Integrate from the cell-local state (base cell c cached) until the ray leaves the box (see
+// Integrate from the cell-local state until the ray leaves the box (see
 // trace_stretch).  Returns the number of steps; sets *limited when max_steps is exceeded.
 template <typename F, int NODES = 0>
 __device__ __forceinline__ int trace_box(const TraceParams &P, CellCache &cc, int c[3], double fd[3],
@@ -563,9 +643,6 @@ __device__ __forceinline__ int trace_box(const TraceParams &P, CellCache &cc, in
 {
     const StepGeom<F> sg = step_geom<F>(P);
     StageCarry<F> carry;
-    carry.have = false;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) carry.aA[a] = (F)0;
     int steps = 0;
     for (;;) {
         const int r = trace_run<F, NODES>(P, cc, c, fd, Wr, dW, carry, sg, steps);
@@ -922,7 +999,6 @@ __device__ __forceinline__ void box_ray(const TraceParams &P, RayState &r)
     F Wr[3], dW[3];
     load_direction(P, r, Wr, dW);
     CellCache cc;
-    first_cell<NODES>(P, r.c, cc);
     bool limited = false;
     const int steps = trace_box<F, NODES>(P, cc, r.c, r.fd, Wr, dW, &limited);
     store_direction<F>(P, r, Wr, dW);
@@ -999,7 +1075,6 @@ __global__ void __launch_bounds__(256, 5) k_box32_refill(TraceParams P, RayState
     float Wr[3], dW[3];
     CellCache cc;
     StageCarry<float> carry;
-    carry.have = false;
     int steps = 0;
     bool drained = false;  // the queue had nothing left for this wave
     for (;;) {
@@ -1018,8 +1093,7 @@ __global__ void __launch_bounds__(256, 5) k_box32_refill(TraceParams P, RayState
                     if ((r.info & (RS_ENTERED | RS_SURR)) == RS_ENTERED) {
                         i = j;
                         load_direction(P, r, Wr, dW);
-                        first_cell<0>(P, r.c, cc);
-                        carry.have = false;
+                        carry = StageCarry<float>();
                         steps = 0;
                     }
                 }
@@ -1072,12 +1146,10 @@ template <int NODES> struct MixedStep {
         }
         const StepGeom<double> sg64 = step_geom<double>(P);
         StageCarry<double> none;
-        none.have = false;
         double W64[3], d64[3] = {0.0, 0.0, 0.0}, f64[3] = {fd[0], fd[1], fd[2]};
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             W64[a] = (double)Wr[a] + (double)dW[a];
-            none.aA[a] = 0.0;
         }
         rkn_step<double, FULL, EDGE, NODES>(P, cc, c, fd, f64, W64, d64, none, sg64, (double)lam);
 #pragma unroll
@@ -1086,6 +1158,7 @@ template <int NODES> struct MixedStep {
             Wr[a] = (float)W;
             dW[a] = (float)(W - (double)Wr[a]);
             f[a] = (float)fd[a];
+            carry.aA[a] = (float)none.aA[a];
         }
         carry.have = false;
         ++n64;
@@ -1101,13 +1174,10 @@ __device__ __forceinline__ int trace_box_mixed(const TraceParams &P, CellCache &
 {
     const StepGeom<float> sg = step_geom<float>(P);
     StageCarry<float> carry;
-    carry.have = false;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) carry.aA[a] = 0.0f;
     MixedStep<NODES> step{P, cc, c, fd, Wr, dW, carry, sg, *n64};
     int steps = 0;
     for (;;) {
-        const int r = trace_stretch<float>(P, c, fd, Wr, dW, sg, steps, step);
+        const int r = trace_stretch<float, NODES>(P, cc, c, fd, Wr, dW, carry, sg, steps, step);
         if (r != STEP_GO) {
             *limited = r == STEP_LIMIT;
             return steps;
@@ -1132,7 +1202,6 @@ __global__ void __launch_bounds__(256, NODES ? 4 : 2) k_box_mixed(TraceParams P,
             float Wr[3], dW[3];
             load_direction(P, r, Wr, dW);
             CellCache cc;
-            first_cell<NODES ? 2 : 0>(P, r.c, cc);
             bool limited = false;
             const int steps = trace_box_mixed<NODES ? 2 : 0>(P, cc, r.c, r.fd, Wr, dW, &limited, &n64);
             store_direction<float>(P, r, Wr, dW);
@@ -1205,9 +1274,6 @@ __global__ void __launch_bounds__(256) k_calibrate(TraceParams P, const int *__r
     load_direction(P, r0, Wr, dW);
     const StepGeom<float> sg = step_geom<float>(P);
     StageCarry<float> a32;
-    a32.have = false;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) a32.aA[a] = 0.0f;
     for (int k = 0; k < n_steps; ++k) rkn_step<float, true, true, L>(P, cc, c32, fd32, f, Wr, dW, a32, sg, 1.0f);
     // FP64
     int c64[3] = {c[0], c[1], c[2]};
@@ -1218,9 +1284,6 @@ __global__ void __launch_bounds__(256) k_calibrate(TraceParams P, const int *__r
     for (int a = 0; a < 3; ++a) W64[a] = P.step_cell[a] * ((double)n0 * u[a]);
     first_cell<L>(P, c64, cc);
     StageCarry<double> a64;
-    a64.have = false;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) a64.aA[a] = 0.0;
     double f64[3] = {fd64[0], fd64[1], fd64[2]};
     for (int k = 0; k < n_steps; ++k) rkn_step<double, true, true, L>(P, cc, c64, fd64, f64, W64, d64, a64, sg64, 1.0);
     double q32[2], q64[2];
