@@ -512,7 +512,7 @@ int pbr_displace_sources(pbr_ctx *ctx, const float *src_in_dev, float *src_out_d
  * decreasing estimated cost per ray (box depth / ds), each split across rounds as needed and
  * padded to whole blocks of 256 rays.  A round is three kernels: emission, a persistent
  * integration kernel in which every wave pulls the next unit_rays rays from a global counter, and
- * lens / sensor / deposit (LDS tile of tile x tile pixels).  The first pbr_batch_run after
+ * lens / sensor / deposit (windows of 2 tile^2 pixels per block in LDS).  The first pbr_batch_run after
  * creation or pbr_batch_configure captures clears, counters and all rounds into one HIP graph;
  * later runs replay it. */
 typedef struct pbr_batch pbr_batch;
@@ -530,7 +530,7 @@ typedef struct pbr_batch_item {
 typedef struct pbr_batch_config {
     int32_t box_block;       /* threads per block of the persistent integration kernel: 64 or 256 */
     int32_t unit_rays;       /* rays a wave pulls from the work queue at a time: 64, 128 or 256 */
-    int32_t tile;            /* deposit pre-aggregation tile side in pixels: 16 or 32 */
+    int32_t tile;            /* deposit pre-aggregation in LDS, 2 tile^2 pixels per block: 16 or 32 */
     int32_t reserved;
     int64_t round_rays;      /* ray states per round, multiple of 256 in [min_round_rays, max_round_rays] */
     int64_t max_round_rays;  /* (out) the largest round the workspace holds */

@@ -130,6 +130,8 @@ void fill_params(const pbr_ctx *ctx, const Derived &d, double ds, TraceParams *o
     }
     for (int a = 0; a < 3; ++a) {
         P.step2_cell[a] = P.h * P.step_cell[a];
+        P.inv_spacing[a] = 1.0 / ctx->spacing[a];
+        P.cell_step[a] = ctx->spacing[a] / P.h;
         P.g32[a] = (float)P.step_cell[a];
     }
     // |D| = |n grad n| anywhere in the box, from the range of the density: a node's derivative is at
@@ -150,6 +152,11 @@ void fill_params(const pbr_ctx *ctx, const Derived &d, double ds, TraceParams *o
     P.pitch = ctx->sensor.pitch;
     P.sigma_px = d.sigma_px;
     P.rfp = d.rfp;
+    P.inv_R = 1.0 / d.R;
+    P.eta_in = d.n_inf / ctx->optics.n_glass;
+    P.eta_out = ctx->optics.n_glass / d.n_inf;
+    P.inv_pitch = 1.0 / ctx->sensor.pitch;
+    P.spot_inv = 1.0 / (1.4142135623730950488 * d.sigma_px);
     P.node_layout = ctx->layout.nodes;
     P.rec = ctx->rec;
     P.rec_first = ctx->rec_first;
@@ -616,11 +623,7 @@ int emit_and_trace_impl(pbr_ctx *ctx, const float *src_dev, int64_t n_src, int32
 
     pbr::TraceParams P;
     fill_params(ctx, d, ds, &P);
-    P.src = (const float4 *)src_dev;
-    P.n_src = n_src;
-    P.rays_per_src = rays_per_src;
-    P.n_rays = n_src * (int64_t)rays_per_src;
-    P.seed = seed;
+    pbr::set_rays(P, (const float4 *)src_dev, n_src, rays_per_src, seed);
     P.record = (flags & PBR_RECORD_EXITS) && ctx->rec_max > 0 ? 1 : 0;
     P.src_sums = (flags & PBR_SOURCE_SUMS) ? ctx->src_sums : nullptr;
     P.order = (flags & PBR_SOURCE_ORDER) && n_src > 0 ? ctx->src_order : nullptr;

@@ -306,11 +306,7 @@ int pbr_batch_create(pbr_batch **out, const pbr_batch_item *items, int n_items, 
             }
             pbr::TraceParams P;
             pbr::host::fill_params(c, d, it.ds, &P);
-            P.src = (const float4 *)it.src_dev;
-            P.n_src = it.n_src;
-            P.rays_per_src = it.rays_per_src;
-            P.n_rays = rays[(size_t)i];
-            P.seed = it.seed;
+            pbr::set_rays(P, (const float4 *)it.src_dev, it.n_src, it.rays_per_src, it.seed);
             P.record = (it.flags & PBR_RECORD_EXITS) && c->rec_max > 0 ? 1 : 0;
             b->params.push_back(P);
             b->versions.push_back(c->param_version);

@@ -117,7 +117,29 @@ struct TraceParams {
     // T over kRunSteps full steps, from the range of the density (see run_budget)
     double step2_cell[3];
     float g32[3], bend32;
+    // reciprocals and quotients of launch constants: 1 / spacing, spacing / h, 1 / R, n_inf / n_glass and
+    // its inverse, 1 / pitch, 1 / (sqrt(2) sigma_px)
+    double inv_spacing[3], cell_step[3];
+    double inv_R, eta_in, eta_out, inv_pitch, spot_inv;
+    // division of 32-bit numbers by rays_per_src as a multiplication (set_rays)
+    uint32_t div_magic, div_sh1, div_sh2, pad2;
 };
+
+// Sources and rays of a launch (32-bit ray positions, see run_of in the trace kernels).
+inline void set_rays(TraceParams &p, const float4 *src, int64_t n_src, int32_t rays_per_src, uint64_t seed)
+{
+    p.src = src;
+    p.n_src = n_src;
+    p.rays_per_src = rays_per_src;
+    p.n_rays = n_src * (int64_t)rays_per_src;
+    p.seed = seed;
+    const uint32_t d = (uint32_t)rays_per_src;
+    uint32_t l = 0;
+    while (l < 32 && ((uint64_t)1 << l) < d) ++l;  // ceil(log2 d)
+    p.div_magic = (uint32_t)((((uint64_t)1 << 32) * (((uint64_t)1 << l) - d)) / d + 1);
+    p.div_sh1 = l < 1 ? l : 1;
+    p.div_sh2 = l < 1 ? 0 : l - 1;
+}
 
 // Offset of the optical chain inside the context's 4 KiB device block (counters come first).
 constexpr size_t kChainOffset = 2048;
@@ -223,7 +245,9 @@ struct ChunkHook {
 // Full steps an integration kernel takes between two tests of the box faces (at most).
 constexpr int kRunSteps = 32;
 
-constexpr int kTile = 32;  // deposit pre-aggregation tile of single-image traces (pixels per side, in LDS)
+// Deposit pre-aggregation in LDS: a block holds 2 * kTile^2 pixels (windows of its sources; a single
+// window too large for that is cut to kTile pixels per side).
+constexpr int kTile = 32;
 
 // One segment of a batch round (see launch_batch_round).
 struct BatchSeg {
@@ -238,7 +262,7 @@ struct BatchSeg {
 struct BatchConfig {
     int box_block;      // threads per block of the persistent integration kernel: 64 or 256
     int unit_rays;      // rays a wave pulls from the queue at a time: 64, 128 or 256
-    int tile;           // deposit tile: 16 or 32 pixels per side
+    int tile;           // deposit windows in LDS: 2 tile^2 pixels per block, tile 16 or 32
     int64_t round_rays; // rays per round (bounded by the workspace)
 };
 

@@ -248,11 +248,7 @@ int check_batch(pbr_surrogate *s, const float *x, const float *t, int64_t rows)
 int trace_samples(pbr_surrogate *s, pbr_ctx *ctx, pbr::TraceParams P, const pbr::SurrogateSpec &spec, int prec,
                   const float *src, int64_t n_src, int32_t rps, uint64_t seed, pbr::SurrogateSample *out)
 {
-    P.src = (const float4 *)src;
-    P.n_src = n_src;
-    P.rays_per_src = rps;
-    P.n_rays = n_src * (int64_t)rps;
-    P.seed = seed;
+    pbr::set_rays(P, (const float4 *)src, n_src, rps, seed);
     P.record = 0;
     for (int64_t first = 0; first < P.n_rays; first += ctx->ray_chunk) {
         const int64_t n = std::min(ctx->ray_chunk, P.n_rays - first);
