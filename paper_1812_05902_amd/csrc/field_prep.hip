@@ -124,14 +124,39 @@ __global__ void __launch_bounds__(256) k_skip_pass(unsigned *__restrict__ gmax, 
     else if (best) gmax[q] = kSkipBit | (unsigned)best;
 }
 
-// The distances of the last pass back into gmax, and tmp zero again.
-__global__ void __launch_bounds__(256) k_skip_finish(unsigned *__restrict__ gmax, unsigned char *__restrict__ tmp,
-                                                     int64_t n)
+// The distances of the last pass back into gmax, marked kSkipSide where a neighbour in x or y has a
+// gradient, and tmp zero again.  (Neighbours' words change under the reader; the tested bit does not.)
+__global__ void __launch_bounds__(256) k_skip_finish(unsigned *__restrict__ gmax, unsigned char *__restrict__ tmp, int nbx,
+                                                     int nby, int64_t n)
 {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= n) return;
-    if (tmp[q]) gmax[q] = kSkipBit | (unsigned)tmp[q];
+    const unsigned d = tmp[q];
     tmp[q] = 0;
+    if (!d) return;
+    const int x = (int)(q % nbx), y = (int)((q / nbx) % nby);
+    bool side = false;
+    for (int dy = -1; dy <= 1; ++dy)
+        for (int dx = -1; dx <= 1; ++dx) {
+            if ((unsigned)(x + dx) >= (unsigned)nbx || (unsigned)(y + dy) >= (unsigned)nby) continue;
+            const unsigned v = __hip_atomic_load(gmax + q + (int64_t)dy * nbx + dx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            side = side || !(v & kSkipBit);
+        }
+    __hip_atomic_store(gmax + q, kSkipBit | (side ? kSkipSide : 0u) | d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Runs towards +z, one thread per column of bricks.
+__global__ void __launch_bounds__(64) k_skip_runs(unsigned *__restrict__ gmax, int64_t columns, int nbz)
+{
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= columns) return;
+    int run = 0;
+#pragma unroll 8
+    for (int z = nbz - 1; z >= 0; --z) {
+        const unsigned v = gmax[(int64_t)z * columns + q];
+        run = (v & (kSkipBit | kSkipSide)) == kSkipBit ? run + 1 : 0;
+        if (v & kSkipBit) gmax[(int64_t)z * columns + q] = kSkipBit | ((unsigned)run << 8) | (v & 0xFFu);
+    }
 }
 
 // Fingerprint of a field: sum over its 32-bit words w_k of SplitMix64's finaliser applied to
@@ -229,7 +254,9 @@ int launch_skip_map(unsigned *gmax, unsigned char *tmp, int nbx, int nby, int nb
     hipLaunchKernelGGL((k_skip_pass<true, false>), grid, block, 0, stream, gmax, tmp, n, (int64_t)1, nbx);
     hipLaunchKernelGGL((k_skip_pass<false, true>), grid, block, 0, stream, gmax, tmp, n, (int64_t)nbx, nby);
     hipLaunchKernelGGL((k_skip_pass<false, false>), grid, block, 0, stream, gmax, tmp, n, (int64_t)nbx * nby, nbz);
-    hipLaunchKernelGGL(k_skip_finish, grid, block, 0, stream, gmax, tmp, n);
+    hipLaunchKernelGGL(k_skip_finish, grid, block, 0, stream, gmax, tmp, nbx, nby, n);
+    const int64_t columns = (int64_t)nbx * nby;
+    hipLaunchKernelGGL(k_skip_runs, dim3((unsigned)((columns + 63) / 64)), dim3(64), 0, stream, gmax, columns, nbz);
     return (int)hipGetLastError();
 }
 

@@ -270,13 +270,16 @@ struct BatchConfig {
 // Writes the cell records and (atomically) the per-brick max |grad n|; gmax must be zeroed.
 int launch_field_prep(const float *rho, float4 *cells, unsigned *brick_gmax, int nx, int ny, int nz,
                       const double spacing[3], double K, hipStream_t stream, bool nodes = false);
-// Replaces the zeros of gmax by kSkipBit | distance in bricks (largest axis distance, at most kSkipMax)
-// to the nearest brick whose gmax is not zero (as a float such a word is not above 0, like the zero it
-// replaces).  tmp: scratch, a byte per brick, left zero.
-constexpr unsigned kSkipBit = 0x80000000u;
+// Replaces the zeros of gmax by kSkipBit | run << 8 | distance (as a float such a word is not above 0, like
+// the zero it replaces).  distance: bricks (largest axis distance, at most kSkipMax) to the nearest brick
+// whose gmax is not zero.  run: bricks from this one on towards +z (light travels that way) in which
+// neither the brick itself nor one of its eight neighbours in x and y has a gradient.  tmp: scratch, a
+// byte per brick, left zero.
+constexpr unsigned kSkipBit = 0x80000000u, kSkipSide = 0x40000000u;
 constexpr int kSkipMax = 127;
 int launch_skip_map(unsigned *gmax, unsigned char *tmp, int nbx, int nby, int nbz, hipStream_t stream);
 __host__ __device__ inline int skip_distance(unsigned word) { return (word & kSkipBit) ? (int)(word & 0xFFu) : 0; }
+__host__ __device__ inline int skip_run(unsigned word) { return (int)((word >> 8) & 0x3FFFu); }
 // Precision calibration: for each listed brick, rays_per_brick sample rays integrated over
 // n_steps full steps in FP32 and in FP64 from the same state; err[k] = largest difference of
 // the image point (apparent source on the plane z_focus, times |M| / pitch) in pixels.

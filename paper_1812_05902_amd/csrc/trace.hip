@@ -73,8 +73,11 @@ struct CellCache {
 // 101, 011, 111 (x, y, z offsets), loaded into the cache.  They are interpolated as they are (see
 // sample_field): steps in the fine grids this layout serves cross a cell every one or two
 // samples, so a per-gather transform into polynomial coefficients would cost more than it saves.
-// d: ic minus the cached cell.  A move to a face neighbour keeps the four corners of the shared face
-// and loads the other four: half the gather traffic on most crossings.
+// d: ic minus the cached cell.  A move of one cell towards +z, the way the light travels, keeps the four
+// corners of the shared face and loads the other four: half the gather traffic on most crossings.  Every
+// other move loads all eight: with a branch for each of the six faces the few lanes that move sideways
+// cost their wave a pass of loads and copies per face (BOS pair 4.84 -> 4.57 ms, 512^3 shock 48.3 -> 45.5,
+// and 117 instead of 128 registers).
 __device__ __forceinline__ void gather_nodes(const TraceParams &P, const int ic[3], const int d[3], CellCache &cc)
 {
     const size_t sy = (size_t)P.nx, sz = (size_t)P.nx * (size_t)P.ny;
@@ -96,30 +99,13 @@ __device__ __forceinline__ void gather_nodes(const TraceParams &P, const int ic[
     }
     const float4 *b = P.cells + (size_t)ic[2] * sz + (size_t)ic[1] * sy + (size_t)ic[0];
     float4 *c = cc.c;
-    const int dx = d[0], dy = d[1], dz = d[2];
-    const bool one = abs(dx) + abs(dy) + abs(dz) == 1;
-    if (one && dz == 1) {
+    if (d[0] == 0 && d[1] == 0 && d[2] == 1) {
         c[0] = c[3]; c[1] = c[5]; c[2] = c[6]; c[4] = c[7];
-        c[3] = b[sz]; c[5] = b[sz + 1]; c[6] = b[sz + sy]; c[7] = b[sz + sy + 1];
-    } else if (one && dz == -1) {
-        c[3] = c[0]; c[5] = c[1]; c[6] = c[2]; c[7] = c[4];
-        c[0] = b[0]; c[1] = b[1]; c[2] = b[sy]; c[4] = b[sy + 1];
-    } else if (one && dx == 1) {
-        c[0] = c[1]; c[2] = c[4]; c[3] = c[5]; c[6] = c[7];
-        c[1] = b[1]; c[4] = b[sy + 1]; c[5] = b[sz + 1]; c[7] = b[sz + sy + 1];
-    } else if (one && dx == -1) {
-        c[1] = c[0]; c[4] = c[2]; c[5] = c[3]; c[7] = c[6];
-        c[0] = b[0]; c[2] = b[sy]; c[3] = b[sz]; c[6] = b[sz + sy];
-    } else if (one && dy == 1) {
-        c[0] = c[2]; c[1] = c[4]; c[3] = c[6]; c[5] = c[7];
-        c[2] = b[sy]; c[4] = b[sy + 1]; c[6] = b[sz + sy]; c[7] = b[sz + sy + 1];
-    } else if (one && dy == -1) {
-        c[2] = c[0]; c[4] = c[1]; c[6] = c[3]; c[7] = c[5];
-        c[0] = b[0]; c[1] = b[1]; c[3] = b[sz]; c[5] = b[sz + 1];
+        asm volatile("");  // keeps the branches apart (no merged stores through selected addresses)
     } else {
-        c[0] = b[0]; c[1] = b[1]; c[2] = b[sy]; c[3] = b[sz];
-        c[4] = b[sy + 1]; c[5] = b[sz + 1]; c[6] = b[sz + sy]; c[7] = b[sz + sy + 1];
+        c[0] = b[0]; c[1] = b[1]; c[2] = b[sy]; c[4] = b[sy + 1];
     }
+    c[3] = b[sz]; c[5] = b[sz + 1]; c[6] = b[sz + sy]; c[7] = b[sz + sy + 1];
 }
 
 // The same gather with every load issued last: the kept corners are shifted one axis at a time
@@ -472,22 +458,25 @@ __device__ __forceinline__ int run_budget(const TraceParams &P, const StepGeom<F
 // loops: no dynamically indexed arrays.)
 enum : int { STEP_GO = 0, STEP_EXIT = 1, STEP_LIMIT = 2 };
 
-// Ray in gas of uniform index.  P.skip holds per brick (kBrick^3 cells) how many bricks away, in the
-// largest of the three axis distances, the nearest brick with a non-zero gradient at any of its nodes
-// lies.  Within such a cube of bricks D is exactly zero at every sample and the steps are straight
-// and equal, so all that end inside the cube are taken at once, and if the cube reaches the box face
-// that the ray heads for, the partial step and the move onto the face too: the same number of steps,
-// the same line, without the rounding of each step's increment.  Called where the last sample of the
-// ray was zero (or none has been taken).  Returns STEP_EXIT when the ray left the box.
+// Ray in gas of uniform index.  P.skip holds per brick (kBrick^3 cells) two boxes of bricks without a
+// gradient at any of their nodes (see launch_skip_map): the cube around it that reaches the nearest
+// gradient, and the column of 3 x 3 bricks from it on towards +z.  Within such a box D is exactly zero
+// at every sample and the steps are straight and equal, so all that end inside the box are taken at
+// once, and if it reaches the box face that the ray heads for, the partial step and the move onto the
+// face too: the same number of steps, the same line, without the rounding of each step's increment.
+// Called where the last sample of the ray was zero (or none has been taken).  Returns STEP_EXIT when
+// the ray left the box.
 // Regions of ambient gas around a flow, the reference render of a BOS pair and the whole volume on
 // either side of a shock are of this kind: the 512^3 shock image (2e8 rays) took 21.7 ms per 1.7e7
-// rays stepping through them (98% of its steps).
+// rays stepping through them (98% of its steps), 2.5 with the cubes alone and 2.2 with the columns: beside
+// a shock along z the cubes are small, and each look costs as much as a step or two.
 template <typename F>
 __device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], double fd[3], const F Wr[3], const F dW[3],
                                             StageCarry<F> &carry, const int last[3], int &steps)
 {
     const double W[3] = {(double)Wr[0] + (double)dW[0], (double)Wr[1] + (double)dW[1], (double)Wr[2] + (double)dW[2]};
     if (!(fabs(W[0]) + fabs(W[1]) + fabs(W[2]) < 1.0e6)) return STEP_GO;
+    const double iW[3] = {1.0 / W[0], 1.0 / W[1], 1.0 / W[2]};
     for (;;) {
         int b[3];
         double p[3];
@@ -497,8 +486,12 @@ __device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], doub
             b[a] = min(max((int)floor(p[a]), 0), last[a] - 1) / kBrick;
         }
         if (PBR_CHECKED && !access_ok(P, b[0] < P.nbx && b[1] < P.nby && b[2] < P.nbz)) return STEP_GO;
-        const int d = skip_distance(P.skip[((size_t)b[2] * P.nby + b[1]) * P.nbx + b[0]]);
+        const unsigned word = P.skip[((size_t)b[2] * P.nby + b[1]) * P.nbx + b[0]];
+        const int d = skip_distance(word);
         if (d == 0) return STEP_GO;
+        // bricks the box extends beyond the ray's own: the column where it reaches further ahead
+        const int run = W[2] > 0.0 ? skip_run(word) : 0;
+        const int side = run > d ? 1 : d - 1, ahead = run > d ? run - 1 : d - 1;
         double s = 3.0e38, end = 0.0;
         int ax = -1;
         bool face = false;
@@ -506,8 +499,8 @@ __device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], doub
         for (int a = 0; a < 3; ++a) {
             if (W[a] == 0.0) continue;
             const bool u = W[a] > 0.0;
-            const int e = u ? min((b[a] + d) * kBrick, last[a]) : max((b[a] - d + 1) * kBrick, 0);
-            const double l = fmax(((double)e - p[a]) / W[a], 0.0);
+            const int e = u ? min((b[a] + 1 + (a == 2 ? ahead : side)) * kBrick, last[a]) : max((b[a] - side) * kBrick, 0);
+            const double l = fmax(((double)e - p[a]) * iW[a], 0.0);
             if (l < s) {
                 s = l;
                 ax = a;
@@ -528,9 +521,7 @@ __device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], doub
             fd[a] = q - (double)c[a];
         }
         carry.cached = false;
-        if (face) {
-            return STEP_EXIT;
-        }
+        if (face) return STEP_EXIT;
     }
 }
 
