@@ -149,6 +149,7 @@ static_assert(kChainOffset >= 8 * (CNT_QUEUE + 1), "optical chain after the coun
 // Per-ray state between the three trace kernels (emit -> box -> finish), 64 bytes.
 // In the box: cell index c, cell fractions fd (FP64), direction T = Tr + dT (Tr at entry).
 // A ray that never entered keeps its world position in fd and its unit direction as Tr + dT.
+// (Arrays of states are laid out by load_state / store_state in the trace kernels, not ray by ray.)
 struct RayState {
     double fd[3];
     float Tr[3];
