@@ -65,9 +65,17 @@ template <> __device__ __forceinline__ int split_cell<double>(double x, double &
 // held in registers.  A ray's position is kept as the integer base cell and a fraction relative to
 // it; a stage point whose fractions all lie in [0, 1) is sampled from the registers as it is, and
 // only a point outside moves the base to its cell (enter_cell).
-struct CellCache {
-    float4 c[kCellFloat4];
+template <typename V> struct CellRecord {
+    V c[kCellFloat4];
 };
+using CellCache = CellRecord<float4>;
+
+// FP64 integration through per-cell records keeps them widened: a record serves about four samples of a
+// wave, and a conversion issues at the rate of an FP64 multiply-add (4.3 cycles per wave), of which
+// a sample takes 28 next to 32 conversions.
+using CellCache64 = CellRecord<double4>;
+template <typename F, int NODES> struct CacheOf { using type = CellCache; };
+template <> struct CacheOf<double, 0> { using type = CellCache64; };
 
 // Node layout: the eight corners (n - 1, grad n) of cell ic, in the order 000, 100, 010, 001, 110,
 // 101, 011, 111 (x, y, z offsets), loaded into the cache.  They are interpolated as they are (see
@@ -175,9 +183,23 @@ __device__ __forceinline__ void gather_cell(const TraceParams &P, const int ic[3
     }
 }
 
-// The first cell of a ray (c inside the grid).
 template <int NODES>
-__device__ __forceinline__ void first_cell(const TraceParams &P, int c[3], CellCache &cc)
+__device__ __forceinline__ void gather_cell(const TraceParams &P, const int ic[3], const int d[3], CellCache64 &cc)
+{
+    static_assert(NODES == 0, "widened records are per cell");
+    CellCache t;
+    gather_cell<0>(P, ic, d, t);
+#pragma unroll
+    for (int k = 0; k < kCellFloat4; ++k) {
+        cc.c[k] = double4{(double)t.c[k].x, (double)t.c[k].y, (double)t.c[k].z, (double)t.c[k].w};
+        // widened here, once per record, and not at each use
+        asm volatile("" : "+v"(cc.c[k].x), "+v"(cc.c[k].y), "+v"(cc.c[k].z), "+v"(cc.c[k].w));
+    }
+}
+
+// The first cell of a ray (c inside the grid).
+template <int NODES, typename C>
+__device__ __forceinline__ void first_cell(const TraceParams &P, int c[3], C &cc)
 {
     if (PBR_CHECKED && !access_ok(P, (unsigned)c[0] <= (unsigned)(P.nx - 2) && (unsigned)c[1] <= (unsigned)(P.ny - 2) &&
                                          (unsigned)c[2] <= (unsigned)(P.nz - 2))) {
@@ -201,8 +223,8 @@ template <> struct UnitOne<double> { static constexpr unsigned value = 0x3FF0000
 // q becomes the fraction inside that cell.  The index is clamped to the grid, which keeps every
 // gather in bounds whatever the values.  EDGE: the point may lie outside the box; it is then moved
 // onto it.
-template <typename F, bool EDGE, int NODES>
-__device__ __forceinline__ void enter_cell(const TraceParams &P, CellCache &cc, int c[3], double fd[3], F f[3], F q[3])
+template <typename F, bool EDGE, int NODES, typename C>
+__device__ __forceinline__ void enter_cell(const TraceParams &P, C &cc, int c[3], double fd[3], F f[3], F q[3])
 {
     const int nmax[3] = {P.nx - 2, P.ny - 2, P.nz - 2};
     int ic[3], d[3];
@@ -243,8 +265,8 @@ __device__ __forceinline__ void enter_cell(const TraceParams &P, CellCache &cc, 
 
 // Trilinear interpolation of (n - 1, grad n) at fractions w of the cached cell.  Returns n - 1, writes
 // G = grad n (D = n G, eq. 6, is formed by the caller).
-template <typename F, int NODES>
-__device__ __forceinline__ F interpolate(const CellCache &cc, const F w[3], F G[3])
+template <typename F, int NODES, typename C>
+__device__ __forceinline__ F interpolate(const C &cc, const F w[3], F G[3])
 {
     const F x = w[0], y = w[1], z = w[2];
     F v[4];
@@ -290,8 +312,8 @@ __device__ __forceinline__ F interpolate(const CellCache &cc, const F w[3], F G[
 // The field at the point q relative to the base cell (fractions anywhere): see enter_cell and
 // interpolate.  Whether the point has left the base cell is one maximum and one compare over all
 // three axes, where finding its cell from scratch takes five slow instructions per axis.
-template <typename F, bool EDGE, int NODES>
-__device__ __forceinline__ F sample_field(const TraceParams &P, CellCache &cc, int c[3], double fd[3], F f[3], F q[3],
+template <typename F, bool EDGE, int NODES, typename C>
+__device__ __forceinline__ F sample_field(const TraceParams &P, C &cc, int c[3], double fd[3], F f[3], F q[3],
                                           F G[3])
 {
     const unsigned m = max(max(unit_word(q[0]), unit_word(q[1])), unit_word(q[2]));
@@ -364,8 +386,8 @@ constexpr float kReuse = 0x1p-25f;
 // every axis, a_C is also the next step's a_A, which saves a third of the samples: nearly all of
 // them in fields as smooth as the turbulence, all but those within the shock in the shock's.  The
 // kernel is bound by VALU issue, where a sample costs 34 instructions and this test five.
-template <typename F, bool FULL, bool EDGE, int NODES>
-__device__ __forceinline__ void rkn_step(const TraceParams &P, CellCache &cc, int c[3], double fd[3], F f[3],
+template <typename F, bool FULL, bool EDGE, int NODES, typename C>
+__device__ __forceinline__ void rkn_step(const TraceParams &P, C &cc, int c[3], double fd[3], F f[3],
                                          const F Wr[3], F dW[3], StageCarry<F> &carry, const StepGeom<F> &sg, F lam)
 {
     constexpr F sixth = (F)1 / (F)6;
@@ -535,8 +557,8 @@ __device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], doub
 // The test of the faces costs about 50 instructions, as much as a fifth of a step; testing once per
 // run of up to kRunSteps = 32 instead of before every step leaves it below 1% of the time, and longer
 // runs let lanes that end a run early wait longer for their wave.
-template <typename F, int NODES, typename Step>
-__device__ __forceinline__ int trace_stretch(const TraceParams &P, CellCache &cc, int c[3], double fd[3], const F Wr[3],
+template <typename F, int NODES, typename Step, typename C>
+__device__ __forceinline__ int trace_stretch(const TraceParams &P, C &cc, int c[3], double fd[3], const F Wr[3],
                                              const F dW[3], StageCarry<F> &carry, const StepGeom<F> &sg, int &steps,
                                              Step &step)
 {
@@ -599,9 +621,9 @@ __device__ __forceinline__ int trace_stretch(const TraceParams &P, CellCache &cc
 }
 
 // The steps of one precision throughout.
-template <typename F, int NODES> struct PlainStep {
+template <typename F, int NODES, typename C> struct PlainStep {
     const TraceParams &P;
-    CellCache &cc;
+    C &cc;
     int *c;
     double *fd;
     const F *Wr;
@@ -618,18 +640,18 @@ template <typename F, int NODES> struct PlainStep {
     }
 };
 
-template <typename F, int NODES = 0>
-__device__ __forceinline__ int trace_run(const TraceParams &P, CellCache &cc, int c[3], double fd[3], const F Wr[3],
+template <typename F, int NODES = 0, typename C>
+__device__ __forceinline__ int trace_run(const TraceParams &P, C &cc, int c[3], double fd[3], const F Wr[3],
                                          F dW[3], StageCarry<F> &carry, const StepGeom<F> &sg, int &steps)
 {
-    PlainStep<F, NODES> step{P, cc, c, fd, Wr, dW, carry, sg};
+    PlainStep<F, NODES, C> step{P, cc, c, fd, Wr, dW, carry, sg};
     return trace_stretch<F, NODES>(P, cc, c, fd, Wr, dW, carry, sg, steps, step);
 }
 
 // Integrate from the cell-local state until the ray leaves the box (see
 // trace_stretch).  Returns the number of steps; sets *limited when max_steps is exceeded.
-template <typename F, int NODES = 0>
-__device__ __forceinline__ int trace_box(const TraceParams &P, CellCache &cc, int c[3], double fd[3],
+template <typename F, int NODES = 0, typename C>
+__device__ __forceinline__ int trace_box(const TraceParams &P, C &cc, int c[3], double fd[3],
                                          const F Wr[3], F dW[3], bool *limited)
 {
     const StepGeom<F> sg = step_geom<F>(P);
@@ -1034,7 +1056,7 @@ __device__ __forceinline__ void box_ray(const TraceParams &P, RayState &r)
 {
     F Wr[3], dW[3];
     load_direction(P, r, Wr, dW);
-    CellCache cc;
+    typename CacheOf<F, NODES>::type cc;
     bool limited = false;
     const int steps = trace_box<F, NODES>(P, cc, r.c, r.fd, Wr, dW, &limited);
     store_direction<F>(P, r, Wr, dW);
@@ -1084,6 +1106,9 @@ __global__ void __launch_bounds__(256, NODES ? 4 : 5) k_box32(TraceParams P, Ray
     box_body<float, NODES>(P, st, n, list, count);
 }
 
+// FP64 integration, bound by VALU issue (every FP64 operation 4.3 cycles per wave).  With the records
+// widened on arrival 149 VGPRs and three waves per SIMD: 500,300 rays through the 64^3 turbulence 2.57 ms
+// a render, 3.17 with the conversions at each sample (a quarter of the instructions, 172 VGPRs).
 template <bool NODES = false>
 __global__ void __launch_bounds__(256) k_box64(TraceParams P, RayState *__restrict__ st, int64_t n,
                                                const int *__restrict__ list,
