@@ -128,7 +128,8 @@ typedef struct pbr_stats {
     uint64_t rkn_steps;                /* Runge-Kutta steps taken (all rays) */
     uint64_t rkn_steps_fp64;           /* of which in FP64 */
     double trace_ms;                   /* device time of the whole trace (HIP events) */
-    double box_ms;                     /* device time of the integration kernel launches alone */
+    double box_ms;                     /* device time of the integration kernel launches alone (emission
+                                          included where they emit their own rays) */
     uint64_t box_launches;             /* integration kernel launches (one per ray chunk) */
     uint64_t surrogate_rays;           /* rays whose box passage the surrogate network replaced */
 } pbr_stats;
