@@ -1131,7 +1131,7 @@ __global__ void __launch_bounds__(256, NODES ? 4 : 5) k_box32(TraceParams P, Ray
 // widened on arrival 149 VGPRs and three waves per SIMD: 500,300 rays through the 64^3 turbulence 2.57 ms
 // a render, 3.17 with the conversions at each sample (a quarter of the instructions, 172 VGPRs).
 template <bool NODES = false>
-__global__ void __launch_bounds__(256) k_box64(TraceParams P, RayState *__restrict__ st, int64_t n,
+__global__ void __launch_bounds__(256, 3) k_box64(TraceParams P, RayState *__restrict__ st, int64_t n,
                                                const int *__restrict__ list,
                                                const unsigned long long *__restrict__ count, int64_t first)
 {
@@ -1267,8 +1267,12 @@ __device__ __forceinline__ int trace_box_mixed(const TraceParams &P, CellCache &
     }
 }
 
+// Waves per SIMD: three with per-cell records (168 VGPRs, the records' conversions kept across samples) are
+// faster than two (169) by 13% where every step is FP64 (500,300 rays, 64^3 turbulence, 4.72 -> 4.09 ms a render)
+// and by 14% where few are (2.5e6 rays, 128^3 shock, 1.19 -> 1.02), and than four with the conversions at each
+// sample (4.47, 1.03).
 template <bool NODES>
-__global__ void __launch_bounds__(256, NODES ? 4 : 2) k_box_mixed(TraceParams P, RayState *__restrict__ st, int64_t n,
+__global__ void __launch_bounds__(256, NODES ? 4 : 3) k_box_mixed(TraceParams P, RayState *__restrict__ st, int64_t n,
                                                    const int *__restrict__ list,
                                                    const unsigned long long *__restrict__ count, int64_t first)
 {
