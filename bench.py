@@ -65,6 +65,19 @@ def _traffic_from_profile(workload="turbulence_bos_128"):
     return d.get("hbm_bytes_per_launch") if d else None
 
 
+def roofline(workload, kernel_ms, method_tflops):
+    """ALU roofline of the integration kernel.  achieved: the FP32 operations it executes per launch
+    (committed counters, when they are of the current kernel source) over the live kernel time, else
+    None.  method_TFLOPs: the operations of all the method's steps over the same time; it is no rate of
+    the chip's and may exceed the peak, since steps through uniform gas are taken at once and the last
+    sample of a step mostly serves as the first of the next."""
+    d = _profile(workload)
+    achieved = d["fp32_flops_per_launch"] / (kernel_ms * 1e-3) / 1e12 if d and "fp32_flops_per_launch" in d else None
+    return {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
+            "frac": achieved / PEAK_FP32_TFLOPS if achieved else None, "method_TFLOPs": method_tflops,
+            "traffic": _traffic_from_profile(workload)}
+
+
 HBM_PEAK_GBS = 8000.0
 GATHER_BYTES_PER_STEP = 384  # the method's field reads per step: 3 evaluations x 8 corners x float4
 
@@ -75,7 +88,7 @@ def memory_roofline(steps_per_launch, kernel_ms, workload="turbulence_bos_128", 
     against the measured L2 read peak."""
     g = steps_per_launch * GATHER_BYTES_PER_STEP / (kernel_ms * 1e-3) / 1e9
     out = {"algorithmic_gather_bytes_per_step": GATHER_BYTES_PER_STEP, "algorithmic_gather_GBps": g}
-    if peaks and peaks.get("l2_read_GBps"):
+    if peaks and peaks.get("l2_read_GBps"):  # above 1: most of the method's reads are never made
         out["algorithmic_gather_over_measured_l2_peak"] = g / peaks["l2_read_GBps"]
     d = _profile(workload)
     if d:
@@ -284,9 +297,7 @@ def bench_turbulence(args, steps=None, warmup=None, peaks=None):
                    "sensor": f"{scene.width}x{scene.height}", "ds_m": scene.ds,
                    "rays_per_chunk": args.rays_per_chunk, "field_layout": layout,
                    "mean_rkn_steps_per_ray": steps_total / steps / n_rays},
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS,
-                     "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_TFLOPS,
-                     "traffic": _traffic_from_profile("turbulence_bos_128"),
+        "roofline": {**roofline("turbulence_bos_128", avg_ms, achieved),
                      "kernel": f"k_box32<{'true' if layout == 'nodes' else 'false'}>",
                      "kernel_ms_per_launch": avg_ms,
                      "launches_per_step": box_launches / steps,
@@ -352,8 +363,7 @@ def bench_batch(args):
                    "node_layout_images": int(sum(use_nodes)),
                    "rounds": st["rounds"], "autotuned": cfg, "probe_rays_per_ms": rate,
                    "mean_rkn_steps_per_ray": steps / args.steps / n_rays, "setup_s": setup_s},
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / PEAK_FP32_TFLOPS, "traffic": None,
+        "roofline": {**roofline(None, 1.0, achieved),
                      "kernel": "whole batch graph (emit + persistent k_box_batch + finish)",
                      "graph_ms_per_step": run_ms / args.steps, "flops_per_rkn_step": flops / max(steps, 1),
                      "rkn_steps_on_nodes": steps_nodes / max(steps, 1)},
@@ -448,8 +458,7 @@ def bench_tomo(args):
                    "rays_per_image": sc.n_rays, "sensor": f"{sc.width}x{sc.height} u16", "ds_m": sc.ds,
                    "mean_rkn_steps_per_ray": steps_total / args.steps / sc.n_rays, "setup_s": setup_s,
                    "field_layout": layout, "source_order": args.source_order},
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / PEAK_FP32_TFLOPS, "traffic": _traffic_from_profile("tomo_piv_512"),
+        "roofline": {**roofline("tomo_piv_512", avg_ms, achieved),
                      "kernel": f"k_box32<{'true' if layout == 'nodes' else 'false'}>",
                      "kernel_ms_per_launch": avg_ms, "launches_per_step": launches / args.steps,
                      "rkn_steps_per_launch": steps_total / launches, "flops_per_rkn_step": fps},
@@ -466,7 +475,8 @@ def bench_tomo(args):
                                    "fp64_bricks": cal_tight["n_fp64"], "steep_bricks": cal_tight["n_steep"],
                                    "rkn_steps_fp64": st_t["rkn_steps_fp64"], "rkn_steps": st_t["rkn_steps"]}
         out["measured_peaks"] = peaks
-        out["roofline"]["frac_of_measured_fp32_fma_rate"] = achieved / peaks["fp32_fma_TFLOPs"]
+        if out["roofline"]["achieved"]:
+            out["roofline"]["frac_of_measured_fp32_fma_rate"] = out["roofline"]["achieved"] / peaks["fp32_fma_TFLOPs"]
         tb = bench_turbulence(args, steps=10, warmup=2, peaks=peaks)
         out["turbulence_bos_128"] = {"rays_per_s": tb["value"], "ms_per_step": tb["ms_per_step"],
                                      "config": tb["config"], "roofline": tb["roofline"], "memory": tb["memory"]}
@@ -537,8 +547,7 @@ def bench_bos_fig4(args):
         "fig4": {"corr_simulated_vs_eq9": float(np.corrcoef(x, y)[0, 1]),
                  "rms_simulated_over_eq9": float(np.sqrt((x * x).mean() / (y * y).mean())),
                  "eq9_max_px": float(np.abs(y).max()), "nodes_filled": int(f.sum())},
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / PEAK_FP32_TFLOPS, "traffic": None, "kernel": "k_box32",
+        "roofline": {**roofline(None, 1.0, achieved), "kernel": "k_box32",
                      "kernel_ms_per_launch": box_ms / launches,
                      "flops_per_rkn_step": FLOPS_PER_STEP["nodes" if nodes else "cells"],
                      "mean_rkn_steps_per_ray": steps_total / args.steps / n_rays},
@@ -601,8 +610,7 @@ def bench_piv_pair(args):
                    "flow": "Lamb-Oseen vortex (0.05 m^2/s, core 1 cm) in a 0.2 m/s stream, 65^3 grid",
                    "frame_interval_s": dt, "max_particle_move_mm": moved * 1e3, "setup_s": setup_s,
                    "field_layout": "nodes" if nodes else "cells"},
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / PEAK_FP32_TFLOPS, "traffic": None, "kernel": "k_box32",
+        "roofline": {**roofline(None, 1.0, achieved), "kernel": "k_box32",
                      "kernel_ms_per_launch": box_ms / launches,
                      "flops_per_rkn_step": FLOPS_PER_STEP["nodes" if nodes else "cells"],
                      "mean_rkn_steps_per_ray": steps_total / args.steps / n_rays},

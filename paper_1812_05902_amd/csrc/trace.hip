@@ -1112,13 +1112,13 @@ __device__ __forceinline__ void box_body(const TraceParams &P, RayState *__restr
     store_state(st, i, n, r);
 }
 
-// FP32 integration: 95 VGPRs, five waves per SIMD.  NODES: field stored per node (the corner gather
+// FP32 integration: 96 VGPRs, five waves per SIMD.  NODES: field stored per node (the corner gather
 // needs more registers: four waves per SIMD).
-// Bound by VALU issue (136 instructions per wave-step, half of wave-steps moving some lane to a new
-// cell) with the L2 misses of those moves behind it.  5e6 rays through the 128^3 turbulence: 15.6 ms a
-// launch, 19.4 ms when every stage point's cell was found from scratch and every step took three
-// samples (203 instructions); 1e7 rays of 256^3 shock with FP64 steps 13.1 against 17.2 ms, the
-// 257^2 x 81 slice 3.9 against 4.8 ms (5.2e6 rays, node layout).
+// Bound by VALU issue (about 140 instructions per wave-step, half of wave-steps moving some lane to a new
+// cell) with the L2 misses of those moves behind it; four waves per SIMD with nothing spilled are 3% slower
+// on the turbulence below.  A render of 5e6 rays through the 128^3 turbulence takes 14.7 ms, 22.9 when
+// every stage point's cell was found from scratch and every step took three samples (203
+// instructions); 5.2e6 rays through the 257^2 x 81 slice (node layout, BOS pair) 4.29 against 11.3 ms.
 template <bool NODES = false>
 __global__ void __launch_bounds__(256, NODES ? 4 : 5) k_box32(TraceParams P, RayState *__restrict__ st, int64_t n,
                                                   const int *__restrict__ list,
