@@ -228,9 +228,9 @@ int pbr_set_density_field_nodes(pbr_ctx *ctx, const float *rho_dev, int nx, int 
                                 double rho_inf, void *ws_dev, size_t ws_bytes);
 
 /* Bytes of trace workspace for chunks of rays_per_chunk rays (64 bytes per ray, at least 256
- * rays).  The trace runs the rays of a call in chunks of this size through three kernels
- * (emission and box entry, ray-equation integration, lens / sensor / deposit) that hand the ray
- * state over in this workspace. */
+ * rays).  The trace runs the rays of a call in chunks of this size through two kernels (emission, box
+ * entry and ray-equation integration; lens / sensor / deposit) that hand the ray state over in this
+ * workspace; with lane refill or a surrogate, emission and box entry are a kernel of their own. */
 size_t pbr_trace_workspace_bytes(int64_t rays_per_chunk);
 
 /* Sets the trace workspace (device, 16-byte aligned, >= pbr_trace_workspace_bytes(256) bytes;
