@@ -128,12 +128,20 @@ void fill_params(const pbr_ctx *ctx, const Derived &d, double ds, TraceParams *o
         P.hi[a] = ctx->origin[a] + (double)(n3[a] - 1) * ctx->spacing[a];
         P.step_cell[a] = P.h / ctx->spacing[a];
     }
+    double g_top = 0.0;
     for (int a = 0; a < 3; ++a) {
         P.step2_cell[a] = P.h * P.step_cell[a];
         P.inv_spacing[a] = 1.0 / ctx->spacing[a];
         P.cell_step[a] = ctx->spacing[a] / P.h;
         P.g32[a] = (float)P.step_cell[a];
+        P.gh32[a] = 0.5f * P.g32[a];
+        g_top = std::fmax(g_top, P.step_cell[a]);
     }
+    P.h32 = (float)P.h;
+    P.h4_32 = 0.25f * P.h32;
+    P.h2_32 = 0.5f * P.h32;
+    P.h6_32 = P.h32 * (1.0f / 6.0f);
+    P.reuse32 = (float)(6.0 * (double)pbr::kReuse / (P.h * g_top));
     // |D| = |n grad n| anywhere in the box, from the range of the density: a node's derivative is at
     // most twice the range over the spacing (the one-sided difference on a face, -3/2, 2, -1/2)
     double slope2 = 0.0;

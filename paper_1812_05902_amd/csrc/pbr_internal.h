@@ -113,10 +113,13 @@ struct TraceParams {
     int pad1;
     // general optical chain (null: the singlet above)
     const pbr_optical_chain *chain;
-    // integration steps: h^2 / spacing; h / spacing in FP32; a bound on the change of any component of
-    // T over kRunSteps full steps, from the range of the density (see run_budget)
+    // integration steps (see StepGeom in the trace kernels): h^2 / spacing; FP32 constants of a full step, rounded
+    // once on the host, g = h / spacing, g / 2, h, h / 4, h / 2, h * (1/6) (float products, as the partial steps
+    // form them); the largest |D_B - D_A| for which a step's last sample serves the next step (kReuse); a bound on
+    // the change of any component of T over kRunSteps full steps, from the range of the density (see
+    // run_budget; zero: the whole field is uniform)
     double step2_cell[3];
-    float g32[3], bend32;
+    float g32[3], gh32[3], h32, h4_32, h2_32, h6_32, reuse32, bend32;
     // reciprocals and quotients of launch constants: 1 / spacing, spacing / h, 1 / R, n_inf / n_glass and
     // its inverse, 1 / pitch, 1 / (sqrt(2) sigma_px)
     double inv_spacing[3], cell_step[3];
@@ -245,6 +248,10 @@ struct ChunkHook {
 
 // Full steps an integration kernel takes between two tests of the box faces (at most).
 constexpr int kRunSteps = 32;
+
+// Largest difference (cells) between the last stage point of a step and its end point for which the
+// sample of the one serves for the other in FP32: half the rounding of a stage point's own fraction.
+constexpr float kReuse = 0x1p-25f;
 
 // Deposit pre-aggregation in LDS: a block holds 2 * kTile^2 pixels (windows of its sources; a single
 // window too large for that is cut to kTile pixels per side).

@@ -329,25 +329,50 @@ __device__ __forceinline__ F sample_field(const TraceParams &P, C &cc, int c[3],
 // Margin (cells) that the steps of a run keep from every face they move towards.
 constexpr float kFaceMargin = 1.0e-3f;
 
-// Per-launch constants of the integration loop.
+// Per-launch constants of the integration loop.  The direction of a ray is carried as V = Vr + dV, the
+// value at the entry plus the accumulated change, in the units of the kernel's field layout:
+//   node layout  V = T, with D = n grad n as the acceleration; a step's increment is g (T + ...), g = h / spacing
+//   cell layout  V = W = h T / spacing (cells per step), with (h^2 / spacing) D as the acceleration: g and h
+//                drop out of the sums, and an increment takes one rounding instead of three
+// Both are eqs. 3 and 5 with g, h, h / 4, h / 2 and h / 6 below.  In FP32 the rounding of the increment is
+// the same at every step of a straight path and makes up most of the error of a hit (512^3 shock: up to 1e-5 px
+// in T, half that in W).  The node layout keeps T: its images are the ones of 1e8 rays and more, where one ray
+// in 1e9 within 1e-6 px of the sensor's border decides a pixel there (with W, two of eight images of 2e8 rays
+// gained or lost a ray against the increments in T, 5e-3 of the rms pixel; 36.6 ms an image against 37.1).
 template <typename F> struct StepGeom {
-    F s[3];        // h^2 / spacing: cells per full step squared, per unit of D
-    int last[3];   // n - 1 per axis (the upper face, in cells)
+    F s[3];                 // cells: h^2 / spacing
+    F g[3], gh[3];          // per unit of V in a full step: cells, half of them
+    F hstep, h4, h2, h6;    // the step, a quarter, half, sixth of it
+    F reuse;                // see rkn_step
+    int last[3];            // n - 1 per axis (the upper face, in cells)
 };
 
-template <typename F> __device__ __forceinline__ StepGeom<F> step_geom(const TraceParams &P)
+template <typename F, int NODES> __device__ __forceinline__ StepGeom<F> step_geom(const TraceParams &P)
 {
+    constexpr bool f32 = sizeof(F) == sizeof(float);
     StepGeom<F> sg;
     const int nn[3] = {P.nx, P.ny, P.nz};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
+        sg.last[a] = nn[a] - 1;
+        if (NODES) {  // FP32: the constants the host rounded once (uniform: scalar registers)
+            sg.g[a] = f32 ? (F)P.g32[a] : (F)P.step_cell[a];
+            sg.gh[a] = f32 ? (F)P.gh32[a] : (F)(0.5 * P.step_cell[a]);
+            continue;
+        }
+        sg.g[a] = (F)1;
+        sg.gh[a] = (F)0.5;
         sg.s[a] = (F)P.step2_cell[a];
         // an FP32 operation with a scalar-register operand issues at half the rate of one on vector
         // registers alone (4.4 against 2.7 cycles per wave measured): the constants of every sample
         // stay in vector registers
-        if (sizeof(F) == sizeof(float)) asm("" : "+v"(sg.s[a]));
-        sg.last[a] = nn[a] - 1;
+        if (f32) asm("" : "+v"(sg.s[a]));
     }
+    sg.hstep = !NODES ? (F)1 : f32 ? (F)P.h32 : (F)P.h;
+    sg.h4 = NODES && f32 ? (F)P.h4_32 : (F)0.25 * sg.hstep;
+    sg.h2 = NODES && f32 ? (F)P.h2_32 : (F)0.5 * sg.hstep;
+    sg.h6 = NODES && f32 ? (F)P.h6_32 : sg.hstep * ((F)1 / (F)6);
+    sg.reuse = NODES ? (F)P.reuse32 : (F)(6.0f * kReuse);
     return sg;
 }
 
@@ -356,83 +381,82 @@ template <typename F> __device__ __forceinline__ StepGeom<F> step_geom(const Tra
 // to the rounding of its density has zero samples everywhere and nothing to skip).
 constexpr int kLookSteps = 4;
 
-// The acceleration at the end point of the step before, when that step's last sample serves for it
-// (see rkn_step).
-// aA is a_C of the step before in any case (zero before the first step); cached: the base cell's
+// The acceleration at the end point of the step before, when that step's last sample serves for it (see
+// rkn_step).
+// D is D_C of the step before in any case (zero before the first step); cached: the base cell's
 // record is loaded; look: steps until a ray whose last sample was zero looks for uniform gas again.
 template <typename F> struct StageCarry {
-    F aA[3] = {(F)0, (F)0, (F)0};
+    F D[3] = {(F)0, (F)0, (F)0};
     bool have = false, cached = false;
     int look = kLookSteps;
 };
 
-// Largest difference (cells) between the last stage point of a step and its end point for which the
-// sample of the one serves for the other: half the rounding of a stage point's own fraction.
-constexpr float kReuse = 0x1p-25f;
-
-// One step of eqs. 3 and 5 of length lam * h in the parameter t (dR/dt = T, dT/dt = D), in cells and
-// full steps: W = h T / spacing (cells per step) and a = h^2 D / spacing (cells per step squared),
-// D = n grad n at the stage points, so that the step length and the spacing drop out of the sums:
-//   stage B point  R + (W + a_A / 4) / 2             (= R + h (T/2 + A/8))
-//   stage C point  R + W + a_B / 2                   (= R + h (T + B/2))
-//   R'             R + W + (a_A + 2 a_B) / 6         (= R + h (T + (A + 2B)/6))
-//   W'             W + (a_A + 4 a_B + a_C) / 6       (= T + (A + 4B + C)/6)
-// The position fd (relative to the base cell) is accumulated in FP64: its increment is nearly the
-// same every step, so FP32 rounding of the running sum would err the same way every step and grow
-// linearly with the step count.  Stage points are formed in F, from f = (F)fd.  W = Wr + dW, Wr its
-// value at the entry: the small increments are summed into a small number.
+// One step of eqs. 3 and 5 of length lam * h in the parameter t (dR/dt = T, dT/dt = D), in
+// cell units (written here with V = T; see StepGeom).  The position fd (relative to the base cell) is
+// accumulated in FP64: its increment is nearly the same every step, so FP32 rounding of the running sum
+// would err the same way every step and grow linearly with the step count.  Stage points are formed
+// in F, from f = (F)fd.
+// With D_A, D_B, D_C the values of D = n grad n at the three stage points, so that eq. 5's
+// A = h D_A, B = h D_B, C = h D_C, the sums are regrouped without forming A, B, C:
+//   stage B point  R + (h/2) (T + (h/4) D_A)        (= R + h (T/2 + A/8))
+//   stage C point  R + h (T + (h/2) D_B)            (= R + h (T + B/2))
+//   R'             R + h (T + (h/6) (D_A + 2 D_B))  (= R + h (T + (A + 2B)/6))
+//   T'             T + (h/6) (D_A + 4 D_B + D_C)    (= T + (A + 4B + C)/6)
+// A partial step (lam = 1) and a full step form the same constants and give the same bits.
 // EDGE: points of the step may lie outside the box (see enter_cell).
-// The stage C point and R' differ by (a_B - a_A) / 6.  In FP32, where that is at most kReuse on
-// every axis, a_C is also the next step's a_A, which saves a third of the samples: nearly all of
-// them in fields as smooth as the turbulence, all but those within the shock in the shock's.  The
-// kernel is bound by VALU issue, where a sample costs 34 instructions and this test five.
+// The stage C point and R' differ by g h (D_B - D_A) / 6.  In FP32, where that is at most kReuse cells on
+// every axis (|D_B - D_A| <= sg.reuse), D_C is also the next step's D_A, which saves a third of the
+// samples: nearly all of them in fields as smooth as the turbulence, all but those within the shock in
+// the shock's.  The kernel is bound by VALU issue, where a sample costs 34 instructions and this test five.
 template <typename F, bool FULL, bool EDGE, int NODES, typename C>
 __device__ __forceinline__ void rkn_step(const TraceParams &P, C &cc, int c[3], double fd[3], F f[3],
-                                         const F Wr[3], F dW[3], StageCarry<F> &carry, const StepGeom<F> &sg, F lam)
+                                         const F Vr[3], F dV[3], StageCarry<F> &carry, const StepGeom<F> &sg, F lam)
 {
-    constexpr F sixth = (F)1 / (F)6;
-    F W[3], acc[3], q[3], aA[3], step[3], sum[3];
-    // a = (h^2 / spacing) n grad n at q
-    auto sample = [&](F out[3]) {
-        F G[3];
-        const F dn = sample_field<F, EDGE, NODES>(P, cc, c, fd, f, q, G);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) out[a] = (sg.s[a] + sg.s[a] * dn) * G[a];
-    };
+    const F hh = FULL ? sg.hstep : lam * sg.hstep;
+    const F h4 = FULL ? sg.h4 : (F)0.25 * hh, h2 = FULL ? sg.h2 : (F)0.5 * hh;
+    const F h6 = FULL ? sg.h6 : hh * ((F)1 / (F)6);
+    F V[3], DA[3], DB[3], G[3], q[3], step[3], sum[3], dn;
+    auto sample = [&] { dn = sample_field<F, EDGE, NODES>(P, cc, c, fd, f, q, G); };
+    // the acceleration at the sampled point
+    auto accel = [&](int a) { return (NODES ? (F)1 + dn : sg.s[a] + sg.s[a] * dn) * G[a]; };
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        W[a] = Wr[a] + dW[a];
-        aA[a] = carry.aA[a];
+        V[a] = Vr[a] + dV[a];
+        DA[a] = carry.D[a];
     }
     if (sizeof(F) == sizeof(double) || !carry.have) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) q[a] = f[a];
-        sample(aA);
+        sample();
+#pragma unroll
+        for (int a = 0; a < 3; ++a) DA[a] = accel(a);
     }
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-        q[a] = FULL ? f[a] + (F)0.5 * (W[a] + (F)0.25 * aA[a]) : f[a] + (F)0.5 * lam * (W[a] + (F)0.25 * lam * aA[a]);
-    sample(acc);
-    // a_A and a_B only through their sums from here on
+    for (int a = 0; a < 3; ++a) {
+        const F gh = FULL ? sg.gh[a] : (F)0.5 * (lam * sg.g[a]);
+        q[a] = f[a] + gh * (V[a] + h4 * DA[a]);
+    }
+    sample();
+    // D_A and D_B only through their sums from here on
     F e = (F)0;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        q[a] = FULL ? f[a] + (W[a] + (F)0.5 * acc[a]) : f[a] + lam * (W[a] + (F)0.5 * lam * acc[a]);
-        if (sizeof(F) == sizeof(float)) e = fmax(e, fabs(acc[a] - aA[a]));
-        const F s2 = aA[a] + (F)2 * acc[a];
-        step[a] = FULL ? W[a] + sixth * s2 : lam * (W[a] + sixth * lam * s2);
-        sum[a] = aA[a] + (F)4 * acc[a];
+        const F gg = FULL ? sg.g[a] : lam * sg.g[a];
+        DB[a] = accel(a);
+        q[a] = f[a] + gg * (V[a] + h2 * DB[a]);
+        if (sizeof(F) == sizeof(float)) e = fmax(e, fabs(DB[a] - DA[a]));
+        step[a] = gg * (V[a] + h6 * (DA[a] + (F)2 * DB[a]));
+        sum[a] = DA[a] + (F)4 * DB[a];
     }
-    sample(aA);
+    sample();
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         fd[a] += (double)step[a];
         f[a] = (F)fd[a];
-        dW[a] = dW[a] + (FULL ? sixth : sixth * lam) * (aA[a] + sum[a]);
+        dV[a] = dV[a] + h6 * (accel(a) + sum[a]);
+        carry.D[a] = accel(a);
     }
-    carry.have = sizeof(F) == sizeof(float) && e <= (F)(6.0f * kReuse);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) carry.aA[a] = aA[a];
+    carry.have = sizeof(F) == sizeof(float) && e <= sg.reuse;
 }
 
 template <typename T> __device__ __forceinline__ T pick3(const T v[3], int k)
@@ -448,12 +472,12 @@ template <typename T> __device__ __forceinline__ T pick3(const T v[3], int k)
 // bound for one step.
 template <typename F>
 __device__ __forceinline__ int run_budget(const TraceParams &P, const StepGeom<F> &sg, const int c[3], const double fd[3],
-                                          const F Wr[3], const F dW[3], int steps)
+                                          const F Vr[3], const F dV[3], int steps)
 {
     float W[3], lo[3], hi[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        W[a] = (float)(Wr[a] + dW[a]);
+        W[a] = (float)(sg.g[a] * (Vr[a] + dV[a]));
         lo[a] = ((float)c[a] + (float)fd[a]) - kFaceMargin;
         hi[a] = ((float)(sg.last[a] - c[a]) - (float)fd[a]) - kFaceMargin;
     }
@@ -485,18 +509,26 @@ enum : int { STEP_GO = 0, STEP_EXIT = 1, STEP_LIMIT = 2 };
 // gradient, and the column of 3 x 3 bricks from it on towards +z.  Within such a box D is exactly zero
 // at every sample and the steps are straight and equal, so all that end inside the box are taken at
 // once, and if it reaches the box face that the ray heads for, the partial step and the move onto the
-// face too: the same number of steps, the same line, without the rounding of each step's increment.
+// face too: the same number of steps.  Cell layout: the same line, without the rounding of each step's
+// increment.  Node layout: each step by the increment that rkn_step rounds (see StepGeom), except where
+// the whole field is uniform: nothing bends a ray there, and it keeps its line to the last bit.
 // Called where the last sample of the ray was zero (or none has been taken).  Returns STEP_EXIT when
 // the ray left the box.
 // Regions of ambient gas around a flow, the reference render of a BOS pair and the whole volume on
 // either side of a shock are of this kind: the 512^3 shock image (2e8 rays) took 21.7 ms per 1.7e7
 // rays stepping through them (98% of its steps), 2.5 with the cubes alone and 2.2 with the columns: beside
 // a shock along z the cubes are small, and each look costs as much as a step or two.
-template <typename F>
-__device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], double fd[3], const F Wr[3], const F dW[3],
-                                            StageCarry<F> &carry, const int last[3], int &steps)
+template <typename F, int NODES>
+__device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], double fd[3], const F Vr[3], const F dV[3],
+                                            StageCarry<F> &carry, const StepGeom<F> &sg, int &steps)
 {
-    const double W[3] = {(double)Wr[0] + (double)dW[0], (double)Wr[1] + (double)dW[1], (double)Wr[2] + (double)dW[2]};
+    const int *last = sg.last;
+    const bool rounded = NODES && P.bend32 != 0.0f;
+    double W[3];  // cells per step
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        W[a] = rounded ? (double)(sg.g[a] * (Vr[a] + dV[a]))
+                       : (NODES ? P.step_cell[a] : 1.0) * ((double)Vr[a] + (double)dV[a]);
     if (!(fabs(W[0]) + fabs(W[1]) + fabs(W[2]) < 1.0e6)) return STEP_GO;
     const double iW[3] = {1.0 / W[0], 1.0 / W[1], 1.0 / W[2]};
     for (;;) {
@@ -535,7 +567,16 @@ __device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], doub
         const int m = face ? (int)ceil(s) : (int)floor(s * (1.0 - 1.0e-12));
         if (!face && m < 1) return STEP_GO;
         steps += m;
-        const double l = face ? s : (double)m;
+        double l = face ? s : (double)m;
+        if (rounded && face) {  // the whole steps, then as the exit rule goes: a step of the rounded fraction, the rest
+            const double whole = (double)max(m - 1, 0);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) p[a] += whole * W[a];
+            const F lam = (F)(end - pick3<double>(p, ax)) / (F)pick3<double>(W, ax);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) p[a] += (double)(lam * sg.g[a] * (Vr[a] + dV[a]));
+            l = (end - pick3<double>(p, ax)) * pick3<double>(iW, ax);
+        }
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const double q = face && a == ax ? end : p[a] + l * W[a];
@@ -558,21 +599,21 @@ __device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], doub
 // run of up to kRunSteps = 32 instead of before every step leaves it below 1% of the time, and longer
 // runs let lanes that end a run early wait longer for their wave.
 template <typename F, int NODES, typename Step, typename C>
-__device__ __forceinline__ int trace_stretch(const TraceParams &P, C &cc, int c[3], double fd[3], const F Wr[3],
-                                             const F dW[3], StageCarry<F> &carry, const StepGeom<F> &sg, int &steps,
+__device__ __forceinline__ int trace_stretch(const TraceParams &P, C &cc, int c[3], double fd[3], const F Vr[3],
+                                             const F dV[3], StageCarry<F> &carry, const StepGeom<F> &sg, int &steps,
                                              Step &step)
 {
-    const bool calm = (carry.aA[0] == (F)0) & (carry.aA[1] == (F)0) & (carry.aA[2] == (F)0);
+    const bool calm = (carry.D[0] == (F)0) & (carry.D[1] == (F)0) & (carry.D[2] == (F)0);
     if (calm && P.skip) {
         const int before = steps;
-        if (skip_uniform<F>(P, c, fd, Wr, dW, carry, sg.last, steps) == STEP_EXIT) return STEP_EXIT;
+        if (skip_uniform<F, NODES>(P, c, fd, Vr, dV, carry, sg, steps) == STEP_EXIT) return STEP_EXIT;
         carry.look = steps > before ? kLookSteps : min(2 * carry.look, kRunSteps);
     }
     if (!carry.cached) {
         first_cell<NODES>(P, c, cc);
         carry.cached = true;
     }
-    int k = run_budget<F>(P, sg, c, fd, Wr, dW, steps);
+    int k = run_budget<F>(P, sg, c, fd, Vr, dV, steps);
     if (calm) k = min(k, carry.look);
     F f[3] = {(F)fd[0], (F)fd[1], (F)fd[2]};
     if (k > 0) {
@@ -586,33 +627,34 @@ __device__ __forceinline__ int trace_stretch(const TraceParams &P, C &cc, int c[
     int ax = -1;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const F v = Wr[a] + dW[a];
+        const F v = sg.g[a] * (Vr[a] + dV[a]);
         F l = (F)3.0e38;
         if (v > (F)0) l = (F)((double)(last[a] - c[a]) - fd[a]) / v;
         else if (v < (F)0) l = (F)((double)(-c[a]) - fd[a]) / v;
         if (l < lam) { lam = l; ax = a; }
     }
     const bool hit = ax >= 0 && lam <= (F)1;
-    const bool up = hit && (pick3<F>(Wr, ax) + pick3<F>(dW, ax)) > (F)0;
+    const bool up = hit && (pick3<F>(Vr, ax) + pick3<F>(dV, ax)) > (F)0;
     // one call site for both the partial step and the edge-extended full step
     if (!hit || lam > (F)0) {
         step.edge(f, hit ? lam : (F)1);
         ++steps;
     }
     if (!hit) return steps > P.max_steps ? STEP_LIMIT : STEP_GO;
-    const F Wn[3] = {Wr[0] + dW[0], Wr[1] + dW[1], Wr[2] + dW[2]};
-    const F Wa = pick3<F>(Wn, ax);
-    if (up ? (Wa > (F)0) : (Wa < (F)0)) {
+    const F Vn[3] = {Vr[0] + dV[0], Vr[1] + dV[1], Vr[2] + dV[2]};
+    const F Va = pick3<F>(Vn, ax);
+    if (up ? (Va > (F)0) : (Va < (F)0)) {
         const int la = pick3<int>(last, ax);
         const double target = up ? (double)la : 0.0;
-        const double l2 = (target - ((double)pick3<int>(c, ax) + pick3<double>(fd, ax))) / (double)Wa;
+        const double l2 = (target - ((double)pick3<int>(c, ax) + pick3<double>(fd, ax))) /
+                          ((double)pick3<F>(sg.g, ax) * (double)Va);
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
             if (b == ax) {
                 c[b] = up ? la - 1 : 0;
                 fd[b] = up ? 1.0 : 0.0;
             } else {
-                fd[b] += l2 * (double)Wn[b];
+                fd[b] += l2 * (double)sg.g[b] * (double)Vn[b];
             }
         }
         return STEP_EXIT;
@@ -626,39 +668,39 @@ template <typename F, int NODES, typename C> struct PlainStep {
     C &cc;
     int *c;
     double *fd;
-    const F *Wr;
-    F *dW;
+    const F *Vr;
+    F *dV;
     StageCarry<F> &carry;
     const StepGeom<F> &sg;
     __device__ __forceinline__ void inside(F f[3])
     {
-        rkn_step<F, true, false, NODES>(P, cc, c, fd, f, Wr, dW, carry, sg, (F)1);
+        rkn_step<F, true, false, NODES>(P, cc, c, fd, f, Vr, dV, carry, sg, (F)1);
     }
     __device__ __forceinline__ void edge(F f[3], F lam)
     {
-        rkn_step<F, false, true, NODES>(P, cc, c, fd, f, Wr, dW, carry, sg, lam);
+        rkn_step<F, false, true, NODES>(P, cc, c, fd, f, Vr, dV, carry, sg, lam);
     }
 };
 
 template <typename F, int NODES = 0, typename C>
-__device__ __forceinline__ int trace_run(const TraceParams &P, C &cc, int c[3], double fd[3], const F Wr[3],
-                                         F dW[3], StageCarry<F> &carry, const StepGeom<F> &sg, int &steps)
+__device__ __forceinline__ int trace_run(const TraceParams &P, C &cc, int c[3], double fd[3], const F Vr[3],
+                                         F dV[3], StageCarry<F> &carry, const StepGeom<F> &sg, int &steps)
 {
-    PlainStep<F, NODES, C> step{P, cc, c, fd, Wr, dW, carry, sg};
-    return trace_stretch<F, NODES>(P, cc, c, fd, Wr, dW, carry, sg, steps, step);
+    PlainStep<F, NODES, C> step{P, cc, c, fd, Vr, dV, carry, sg};
+    return trace_stretch<F, NODES>(P, cc, c, fd, Vr, dV, carry, sg, steps, step);
 }
 
 // Integrate from the cell-local state until the ray leaves the box (see
 // trace_stretch).  Returns the number of steps; sets *limited when max_steps is exceeded.
 template <typename F, int NODES = 0, typename C>
 __device__ __forceinline__ int trace_box(const TraceParams &P, C &cc, int c[3], double fd[3],
-                                         const F Wr[3], F dW[3], bool *limited)
+                                         const F Vr[3], F dV[3], bool *limited)
 {
-    const StepGeom<F> sg = step_geom<F>(P);
+    const StepGeom<F> sg = step_geom<F, NODES>(P);
     StageCarry<F> carry;
     int steps = 0;
     for (;;) {
-        const int r = trace_run<F, NODES>(P, cc, c, fd, Wr, dW, carry, sg, steps);
+        const int r = trace_run<F, NODES>(P, cc, c, fd, Vr, dV, carry, sg, steps);
         if (r != STEP_GO) {
             *limited = r == STEP_LIMIT;
             return steps;
@@ -1022,32 +1064,35 @@ __global__ void __launch_bounds__(256) k_emit(TraceParams P, RayState *__restric
 
 // ------------------------------------------------------------------ kernel 2: the ray equation
 
-// W = h T / spacing of a state as the integration carries it: a float hi/lo pair in FP32 (about 48
-// significant bits, no rounding of the entry direction), one double in FP64.
-__device__ __forceinline__ void load_direction(const TraceParams &P, const RayState &r, float Wr[3], float dW[3])
+// V of a state as the integration carries it (see StepGeom): a float hi/lo pair in FP32 (about 48
+// significant bits, no rounding of the entry direction; its low part starts the accumulated change), one
+// double in FP64.
+template <int NODES>
+__device__ __forceinline__ void load_direction(const TraceParams &P, const RayState &r, float Vr[3], float dV[3])
 {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const double W = P.step_cell[a] * ((double)r.Tr[a] + (double)r.dT[a]);
-        Wr[a] = (float)W;
-        dW[a] = (float)(W - (double)Wr[a]);
+        const double V = (NODES ? 1.0 : P.step_cell[a]) * ((double)r.Tr[a] + (double)r.dT[a]);
+        Vr[a] = NODES ? r.Tr[a] : (float)V;
+        dV[a] = NODES ? r.dT[a] : (float)(V - (double)Vr[a]);
     }
 }
-__device__ __forceinline__ void load_direction(const TraceParams &P, const RayState &r, double Wr[3], double dW[3])
+template <int NODES>
+__device__ __forceinline__ void load_direction(const TraceParams &P, const RayState &r, double Vr[3], double dV[3])
 {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        Wr[a] = P.step_cell[a] * ((double)r.Tr[a] + (double)r.dT[a]);
-        dW[a] = 0.0;
+        Vr[a] = (NODES ? 1.0 : P.step_cell[a]) * ((double)r.Tr[a] + (double)r.dT[a]);
+        dV[a] = 0.0;
     }
 }
-// T back from W, as a float hi/lo pair.
-template <typename F>
-__device__ __forceinline__ void store_direction(const TraceParams &P, RayState &r, const F Wr[3], const F dW[3])
+// T back from V, as a float hi/lo pair.
+template <typename F, int NODES>
+__device__ __forceinline__ void store_direction(const TraceParams &P, RayState &r, const F Vr[3], const F dV[3])
 {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const double T = ((double)Wr[a] + (double)dW[a]) * P.cell_step[a];
+        const double T = ((double)Vr[a] + (double)dV[a]) * (NODES ? 1.0 : P.cell_step[a]);
         r.Tr[a] = (float)T;
         r.dT[a] = (float)(T - (double)r.Tr[a]);
     }
@@ -1056,12 +1101,12 @@ __device__ __forceinline__ void store_direction(const TraceParams &P, RayState &
 template <typename F, int NODES = 0>
 __device__ __forceinline__ void box_ray(const TraceParams &P, RayState &r)
 {
-    F Wr[3], dW[3];
-    load_direction(P, r, Wr, dW);
+    F Vr[3], dV[3];
+    load_direction<NODES>(P, r, Vr, dV);
     typename CacheOf<F, NODES>::type cc;
     bool limited = false;
-    const int steps = trace_box<F, NODES>(P, cc, r.c, r.fd, Wr, dW, &limited);
-    store_direction<F>(P, r, Wr, dW);
+    const int steps = trace_box<F, NODES>(P, cc, r.c, r.fd, Vr, dV, &limited);
+    store_direction<F, NODES>(P, r, Vr, dV);
     r.info = RS_ENTERED | (limited ? RS_LIMITED : 0) | (steps << RS_STEP_SHIFT);
 }
 
@@ -1151,10 +1196,10 @@ __global__ void __launch_bounds__(256, 5) k_box32_refill(TraceParams P, RayState
     if (P.node_layout) return;  // cell records only (the host never launches it otherwise)
     const int lane = threadIdx.x & 63;
     const unsigned long long total = list ? *count : (unsigned long long)n;
-    const StepGeom<float> sg = step_geom<float>(P);
+    const StepGeom<float> sg = step_geom<float, 0>(P);
     int64_t i = -1;  // this lane's ray, -1: none
     RayState r;
-    float Wr[3], dW[3];
+    float Vr[3], dV[3];
     CellCache cc;
     StageCarry<float> carry;
     int steps = 0;
@@ -1174,7 +1219,7 @@ __global__ void __launch_bounds__(256, 5) k_box32_refill(TraceParams P, RayState
                     r = load_state(st, j, n);
                     if ((r.info & (RS_ENTERED | RS_SURR)) == RS_ENTERED) {
                         i = j;
-                        load_direction(P, r, Wr, dW);
+                        load_direction<0>(P, r, Vr, dV);
                         carry = StageCarry<float>();
                         steps = 0;
                     }
@@ -1184,9 +1229,9 @@ __global__ void __launch_bounds__(256, 5) k_box32_refill(TraceParams P, RayState
         }
         if (__ballot(i >= 0) == 0) break;  // queue drained and no lane busy
         if (i >= 0) {
-            const int res = trace_run<float>(P, cc, r.c, r.fd, Wr, dW, carry, sg, steps);
+            const int res = trace_run<float>(P, cc, r.c, r.fd, Vr, dV, carry, sg, steps);
             if (res != STEP_GO) {
-                store_direction<float>(P, r, Wr, dW);
+                store_direction<float, 0>(P, r, Vr, dV);
                 r.info = RS_ENTERED | (res == STEP_LIMIT ? RS_LIMITED : 0) | (steps << RS_STEP_SHIFT);
                 store_state(st, i, n, r);
                 i = -1;
@@ -1208,14 +1253,14 @@ __device__ __forceinline__ bool brick_is_fp64(const TraceParams &P, const int c[
 }
 
 // Steps whose precision is chosen one by one from the brick of the ray's current cell: FP64 from the
-// FP32 state (W = Wr + dW carried in double through the step, then split again into a float hi/lo
+// FP32 state (V = Vr + dV carried in double through the step, then split again into a float hi/lo
 // pair), or FP32.
 template <int NODES> struct MixedStep {
     const TraceParams &P;
     CellCache &cc;
     int *c;
     double *fd;
-    float *Wr, *dW;
+    float *Vr, *dV;
     StageCarry<float> &carry;
     const StepGeom<float> &sg;
     int &n64;
@@ -1223,24 +1268,22 @@ template <int NODES> struct MixedStep {
     {
         const int cell[3] = {c[0] + (int)floorf(f[0]), c[1] + (int)floorf(f[1]), c[2] + (int)floorf(f[2])};
         if (!brick_is_fp64(P, cell)) {
-            rkn_step<float, FULL, EDGE, NODES>(P, cc, c, fd, f, Wr, dW, carry, sg, lam);
+            rkn_step<float, FULL, EDGE, NODES>(P, cc, c, fd, f, Vr, dV, carry, sg, lam);
             return;
         }
-        const StepGeom<double> sg64 = step_geom<double>(P);
+        const StepGeom<double> sg64 = step_geom<double, NODES>(P);
         StageCarry<double> none;
-        double W64[3], d64[3] = {0.0, 0.0, 0.0}, f64[3] = {fd[0], fd[1], fd[2]};
+        double V64[3], d64[3] = {0.0, 0.0, 0.0}, f64[3] = {fd[0], fd[1], fd[2]};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) V64[a] = (double)Vr[a] + (double)dV[a];
+        rkn_step<double, FULL, EDGE, NODES>(P, cc, c, fd, f64, V64, d64, none, sg64, (double)lam);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            W64[a] = (double)Wr[a] + (double)dW[a];
-        }
-        rkn_step<double, FULL, EDGE, NODES>(P, cc, c, fd, f64, W64, d64, none, sg64, (double)lam);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const double W = W64[a] + d64[a];
-            Wr[a] = (float)W;
-            dW[a] = (float)(W - (double)Wr[a]);
+            const double V = V64[a] + d64[a];
+            Vr[a] = (float)V;
+            dV[a] = (float)(V - (double)Vr[a]);
             f[a] = (float)fd[a];
-            carry.aA[a] = (float)none.aA[a];
+            carry.D[a] = (float)none.D[a];
         }
         carry.have = false;
         ++n64;
@@ -1252,14 +1295,14 @@ template <int NODES> struct MixedStep {
 // trace_box<float> with the step precision chosen per step.
 template <int NODES>
 __device__ __forceinline__ int trace_box_mixed(const TraceParams &P, CellCache &cc, int c[3], double fd[3],
-                                               float Wr[3], float dW[3], bool *limited, int *n64)
+                                               float Vr[3], float dV[3], bool *limited, int *n64)
 {
-    const StepGeom<float> sg = step_geom<float>(P);
+    const StepGeom<float> sg = step_geom<float, NODES>(P);
     StageCarry<float> carry;
-    MixedStep<NODES> step{P, cc, c, fd, Wr, dW, carry, sg, *n64};
+    MixedStep<NODES> step{P, cc, c, fd, Vr, dV, carry, sg, *n64};
     int steps = 0;
     for (;;) {
-        const int r = trace_stretch<float, NODES>(P, cc, c, fd, Wr, dW, carry, sg, steps, step);
+        const int r = trace_stretch<float, NODES>(P, cc, c, fd, Vr, dV, carry, sg, steps, step);
         if (r != STEP_GO) {
             *limited = r == STEP_LIMIT;
             return steps;
@@ -1285,12 +1328,12 @@ __global__ void __launch_bounds__(256, NODES ? 4 : 3) k_box_mixed(TraceParams P,
     if (live) {
         RayState r;
         if (start_state(P, st, i, n, first, r)) {
-            float Wr[3], dW[3];
-            load_direction(P, r, Wr, dW);
+            float Vr[3], dV[3];
+            load_direction<NODES>(P, r, Vr, dV);
             CellCache cc;
             bool limited = false;
-            const int steps = trace_box_mixed<NODES ? 2 : 0>(P, cc, r.c, r.fd, Wr, dW, &limited, &n64);
-            store_direction<float>(P, r, Wr, dW);
+            const int steps = trace_box_mixed<NODES ? 2 : 0>(P, cc, r.c, r.fd, Vr, dV, &limited, &n64);
+            store_direction<float, NODES>(P, r, Vr, dV);
             r.info = RS_ENTERED | (limited ? RS_LIMITED : 0) | (steps << RS_STEP_SHIFT);
             store_state(st, i, n, r);
         }
@@ -1356,22 +1399,22 @@ __global__ void __launch_bounds__(256) k_calibrate(TraceParams P, const int *__r
         r0.Tr[a] = (float)T0;
         r0.dT[a] = (float)(T0 - (double)r0.Tr[a]);
     }
-    float Wr[3], dW[3];
-    load_direction(P, r0, Wr, dW);
-    const StepGeom<float> sg = step_geom<float>(P);
+    float Vr[3], dV[3];
+    load_direction<L>(P, r0, Vr, dV);
+    const StepGeom<float> sg = step_geom<float, L>(P);
     StageCarry<float> a32;
-    for (int k = 0; k < n_steps; ++k) rkn_step<float, true, true, L>(P, cc, c32, fd32, f, Wr, dW, a32, sg, 1.0f);
+    for (int k = 0; k < n_steps; ++k) rkn_step<float, true, true, L>(P, cc, c32, fd32, f, Vr, dV, a32, sg, 1.0f);
     // FP64
     int c64[3] = {c[0], c[1], c[2]};
     double fd64[3] = {fd[0], fd[1], fd[2]};
-    double W64[3], d64[3] = {0.0, 0.0, 0.0};
-    const StepGeom<double> sg64 = step_geom<double>(P);
+    double V64[3], d64[3] = {0.0, 0.0, 0.0};
+    const StepGeom<double> sg64 = step_geom<double, L>(P);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) W64[a] = P.step_cell[a] * ((double)n0 * u[a]);
+    for (int a = 0; a < 3; ++a) V64[a] = (L ? 1.0 : P.step_cell[a]) * ((double)n0 * u[a]);
     first_cell<L>(P, c64, cc);
     StageCarry<double> a64;
     double f64[3] = {fd64[0], fd64[1], fd64[2]};
-    for (int k = 0; k < n_steps; ++k) rkn_step<double, true, true, L>(P, cc, c64, fd64, f64, W64, d64, a64, sg64, 1.0);
+    for (int k = 0; k < n_steps; ++k) rkn_step<double, true, true, L>(P, cc, c64, fd64, f64, V64, d64, a64, sg64, 1.0);
     double q32[2], q64[2];
     {
         double Xa[3], Xb[3], da[3], db[3];
@@ -1379,8 +1422,9 @@ __global__ void __launch_bounds__(256) k_calibrate(TraceParams P, const int *__r
         for (int a = 0; a < 3; ++a) {
             Xa[a] = P.origin[a] + ((double)c32[a] + fd32[a]) * P.spacing[a];
             Xb[a] = P.origin[a] + ((double)c64[a] + fd64[a]) * P.spacing[a];
-            da[a] = ((double)Wr[a] + (double)dW[a]) / P.step_cell[a];
-            db[a] = (W64[a] + d64[a]) / P.step_cell[a];
+            const double unit = L ? 1.0 : P.step_cell[a];
+            da[a] = ((double)Vr[a] + (double)dV[a]) / unit;
+            db[a] = (V64[a] + d64[a]) / unit;
         }
         const double ta = (Xa[2] - z_focus) / da[2], tb = (Xb[2] - z_focus) / db[2];
         q32[0] = Xa[0] - ta * da[0]; q32[1] = Xa[1] - ta * da[1];
