@@ -46,9 +46,7 @@ k_field_prep(const float *__restrict__ rho, float4 *__restrict__ out, unsigned *
     __shared__ double sv[NODES ? 1 : kNodes][4];
     __shared__ double sg[4];
     __shared__ float4 stage[NODES ? 1 : 4][NODES ? 1 : 64 * kCellFloat4];
-    const int nbx = (nx - 1 + kBrick - 1) / kBrick, nby = (ny - 1 + kBrick - 1) / kBrick;
-    const int bx = (int)(blockIdx.x % nbx), by = (int)((blockIdx.x / nbx) % nby), bz = (int)(blockIdx.x / (nbx * nby));
-    const int i0 = bx * kBrick, j0 = by * kBrick, k0 = bz * kBrick;
+    const int i0 = (int)blockIdx.x * kBrick, j0 = (int)blockIdx.y * kBrick, k0 = (int)blockIdx.z * kBrick;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const size_t sy = (size_t)nx, sz = (size_t)nx * (size_t)ny;
     for (int t = threadIdx.x; t < kHalo * kHalo * kHalo; t += 256) {
@@ -85,7 +83,7 @@ k_field_prep(const float *__restrict__ rho, float4 *__restrict__ out, unsigned *
     __syncthreads();
     if (threadIdx.x == 0) {
         const float gf = (float)sqrt(fmax(fmax(sg[0], sg[1]), fmax(sg[2], sg[3])));
-        brick_gmax[blockIdx.x] = gf > 0.0f ? __float_as_uint(gf) : 0u;
+        brick_gmax[((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = gf > 0.0f ? __float_as_uint(gf) : 0u;
     }
     if (NODES) return;
     for (int slab = wave; slab < kBrick; slab += 4) {  // 64 cells of one z per wave
@@ -298,7 +296,8 @@ int launch_field_prep(const float *rho, float4 *cells, unsigned *brick_gmax, int
                       const double spacing[3], double K, hipStream_t stream, bool nodes)
 {
     const FieldLayout L = field_layout(nx, ny, nz, nodes);
-    const dim3 grid((unsigned)L.n_bricks), block(256);
+    // one dimension per axis: a thin grid can have 2^24 bricks and more, whose threads no single one counts
+    const dim3 grid((unsigned)L.nbx, (unsigned)L.nby, (unsigned)L.nbz), block(256);
     if (nodes)
         hipLaunchKernelGGL(k_field_prep<true>, grid, block, 0, stream, rho, cells, brick_gmax, nx, ny, nz, K / spacing[0],
                            K / spacing[1], K / spacing[2], K);
