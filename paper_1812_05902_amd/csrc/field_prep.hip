@@ -49,7 +49,8 @@ k_field_prep(const float *__restrict__ rho, float4 *__restrict__ out, unsigned *
     const int i0 = (int)blockIdx.x * kBrick, j0 = (int)blockIdx.y * kBrick, k0 = (int)blockIdx.z * kBrick;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const size_t sy = (size_t)nx, sz = (size_t)nx * (size_t)ny;
-    for (int t = threadIdx.x; t < kHalo * kHalo * kHalo; t += 256) {
+    // (no planes beyond the grid: slices a few nodes deep along z)
+    for (int t = threadIdx.x; t < kHalo * kHalo * min(kHalo, nz - k0 + 1); t += 256) {
         const int x = t % kHalo, y = (t / kHalo) % kHalo, z = t / (kHalo * kHalo);
         // nodes beyond the grid are not used
         const int i = min(max(i0 + x - 1, 0), nx - 1), j = min(max(j0 + y - 1, 0), ny - 1),
@@ -58,10 +59,10 @@ k_field_prep(const float *__restrict__ rho, float4 *__restrict__ out, unsigned *
     }
     __syncthreads();
     double gm = 0.0;
-    for (int t = threadIdx.x; t < kNodes; t += 256) {
+    for (int t = threadIdx.x; t < kSide * kSide * min(kSide, nz - k0); t += 256) {
         const int x = t % kSide, y = (t / kSide) % kSide, z = t / (kSide * kSide);
         const int i = i0 + x, j = j0 + y, k = k0 + z;
-        if (i >= nx || j >= ny || k >= nz) continue;
+        if (i >= nx || j >= ny) continue;
         const int q = ((z + 1) * kHalo + y + 1) * kHalo + x + 1;
         const double d0 = (double)sr[q], v0 = K * d0, v1 = kx * index_derivative(sr, q, 1, i, nx),
                      v2 = ky * index_derivative(sr, q, kHalo, j, ny),
@@ -143,11 +144,59 @@ k_field_prep(const float *__restrict__ rho, float4 *__restrict__ out, unsigned *
     }
 }
 
-// One axis of the distance map: the least over r of max(r, distance so far at r bricks along the axis
-// on either side).  Taken along x, then y, then z from 0 / kSkipMax this gives the largest-axis
-// distance to the nearest marked brick.  FIRST reads the gradients themselves; WORDS: from the bytes of
-// tmp into the words of gmax, otherwise from the words into the bytes.  A few thousand to a few hundred
-// thousand bricks: launch-bound.
+// One axis of the distance map at brick q, the i-th of `len` along the axis: the least over r of
+// max(r, distance so far at r bricks along the axis on either side).  Taken along x, then y, then z from
+// 0 / kSkipMax this gives the largest-axis distance to the nearest marked brick.
+template <typename At>
+__device__ __forceinline__ int axis_distance(At at, int64_t q, int64_t stride, int i, int len)
+{
+    int best = at(q);
+    for (int r = 1; r < best; ++r) {
+        if (i - r < 0 && i + r >= len) break;
+        if (i - r >= 0) best = min(best, max(r, at(q - r * stride)));
+        if (i + r < len) best = min(best, max(r, at(q + r * stride)));
+    }
+    return best;
+}
+
+// The whole map of a grid of at most kSkipSmall bricks by one block, in LDS: one launch in place of the five
+// below, which are most of what a small field waits for (pbr_set_density_field with 33^3 nodes 78 -> 39 us, 65^3
+// 76 -> 45; 131 x 100 x 77, 2210 bricks, 98 -> 78).  Beyond, one block's passes would take longer than the launches.
+constexpr int kSkipSmall = 4096;
+__global__ void __launch_bounds__(1024) k_skip_small(unsigned *__restrict__ gmax, int nbx, int nby, int nbz)
+{
+    __shared__ unsigned char a[kSkipSmall], b[kSkipSmall];
+    const int columns = nbx * nby, n = columns * nbz;
+    for (int q = threadIdx.x; q < n; q += blockDim.x) a[q] = gmax[q] ? 0 : kSkipMax;
+    __syncthreads();
+    auto pass = [&](const unsigned char *from, unsigned char *to, int stride, int len) {
+        for (int q = threadIdx.x; q < n; q += blockDim.x)
+            to[q] = (unsigned char)axis_distance([&](int64_t k) { return (int)from[k]; }, q, stride, (q / stride) % len, len);
+        __syncthreads();
+    };
+    pass(a, b, 1, nbx);
+    pass(b, a, nbx, nby);
+    pass(a, b, columns, nbz);
+    for (int q = threadIdx.x; q < n; q += blockDim.x) {  // a: none of the brick and its neighbours in x and y has a gradient
+        const int x = q % nbx, y = (q / nbx) % nby;
+        bool open = true;
+        for (int dy = -1; dy <= 1; ++dy)
+            for (int dx = -1; dx <= 1; ++dx)
+                if ((unsigned)(x + dx) < (unsigned)nbx && (unsigned)(y + dy) < (unsigned)nby) open = open && b[q + dy * nbx + dx];
+        a[q] = open;
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < columns; c += blockDim.x) {
+        int run = 0;
+        for (int q = n - columns + c; q >= 0; q -= columns) {
+            run = a[q] ? run + 1 : 0;
+            if (b[q]) gmax[q] = kSkipBit | ((unsigned)run << 8) | b[q];
+        }
+    }
+}
+
+// One axis of the distance map of a larger grid.  FIRST reads the gradients themselves; WORDS: from the
+// bytes of tmp into the words of gmax, otherwise from the words into the bytes.
 template <bool FIRST, bool WORDS>
 __global__ void __launch_bounds__(256) k_skip_pass(unsigned *__restrict__ gmax, unsigned char *__restrict__ tmp, int64_t n,
                                                    int64_t stride, int len)
@@ -160,12 +209,7 @@ __global__ void __launch_bounds__(256) k_skip_pass(unsigned *__restrict__ gmax, 
         const unsigned v = gmax[k];
         return FIRST ? (v ? 0 : kSkipMax) : skip_distance(v);
     };
-    int best = at(q);
-    for (int r = 1; r < best; ++r) {
-        if (i - r < 0 && i + r >= len) break;
-        if (i - r >= 0) best = min(best, max(r, at(q - r * stride)));
-        if (i + r < len) best = min(best, max(r, at(q + r * stride)));
-    }
+    const int best = axis_distance(at, q, stride, i, len);
     if (!WORDS) tmp[q] = (unsigned char)best;
     else if (best) gmax[q] = kSkipBit | (unsigned)best;
 }
@@ -310,6 +354,10 @@ int launch_field_prep(const float *rho, float4 *cells, unsigned *brick_gmax, int
 int launch_skip_map(unsigned *gmax, unsigned char *tmp, int nbx, int nby, int nbz, hipStream_t stream)
 {
     const int64_t n = (int64_t)nbx * nby * nbz;
+    if (n <= kSkipSmall) {
+        hipLaunchKernelGGL(k_skip_small, dim3(1), dim3(1024), 0, stream, gmax, nbx, nby, nbz);
+        return (int)hipGetLastError();
+    }
     const dim3 grid((unsigned)((n + 255) / 256)), block(256);
     hipLaunchKernelGGL((k_skip_pass<true, false>), grid, block, 0, stream, gmax, tmp, n, (int64_t)1, nbx);
     hipLaunchKernelGGL((k_skip_pass<false, true>), grid, block, 0, stream, gmax, tmp, n, (int64_t)nbx, nby);
