@@ -614,7 +614,7 @@ __device__ __forceinline__ int trace_stretch(const TraceParams &P, C &cc, int c[
         carry.cached = true;
     }
     int k = run_budget<F>(P, sg, c, fd, Vr, dV, steps);
-    if (calm) k = min(k, carry.look);
+    if (calm && P.skip) k = min(k, carry.look);
     F f[3] = {(F)fd[0], (F)fd[1], (F)fd[2]};
     if (k > 0) {
         steps += k;
