@@ -399,7 +399,7 @@ int set_field(pbr_ctx *ctx, const float *rho_dev, int nx, int ny, int nz, const 
     ctx->brick_gmax = (unsigned *)(base + L.gmax_off);
     ctx->brick_fp64 = (unsigned char *)(base + L.flags_off);
     ctx->n_fp64_bricks = 0;
-    ctx->flags_written = false;
+    ctx->flags_uniform = false;
     ctx->cells = (const float4 *)(base + L.cells_off);
     ctx->nx = nx; ctx->ny = ny; ctx->nz = nz;
     for (int a = 0; a < 3; ++a) { ctx->origin[a] = origin[a]; ctx->spacing[a] = spacing[a]; }
@@ -645,8 +645,8 @@ int emit_and_trace_impl(pbr_ctx *ctx, const float *src_dev, int64_t n_src, int32
     const int prec = (flags & PBR_PREC_FP64_ALL) ? pbr::PREC_FP64
                      : ((flags & PBR_PREC_SHOCK_FP64) && ctx->n_fp64_bricks > 0) ? pbr::PREC_MIXED
                      : pbr::PREC_FP32;
-    // flags of the caller's own may ask for FP64 steps in gas without a gradient: count and take them
-    if (prec == pbr::PREC_MIXED && ctx->flags_written) P.skip = nullptr;
+    // FP64 steps asked for in gas without a gradient: count and take them
+    if (prec == pbr::PREC_MIXED && ctx->flags_uniform) P.skip = nullptr;
     const int64_t n_chunks = (P.n_rays + ray_chunk - 1) / ray_chunk;
     // per-launch timing events (created on demand, so not in the allocation-free variant)
     const bool launch_ev = stats && !noalloc;
@@ -789,7 +789,7 @@ int pbr_calibrate_precision(pbr_ctx *ctx, double tol_px, double steep_frac, int3
     if (!e) e = (int)hipStreamSynchronize(ctx->stream);
     if (e) return hip_fail(ctx, e, "write brick flags");
     ctx->n_fp64_bricks = nf;
-    ctx->flags_written = false;
+    ctx->flags_uniform = false;
     if (out) {
         out->n_bricks = nb;
         out->n_steep = ns;
@@ -817,13 +817,19 @@ int pbr_brick_flags(pbr_ctx *ctx, uint8_t *inout_host, int64_t n_bricks, int wri
     if (!g.ok) return fail(ctx, PBR_ERR_HIP, "hipSetDevice failed");
     int e;
     if (write) {
-        int64_t nf = 0;
-        for (int64_t b = 0; b < n_bricks; ++b) nf += inout_host[b] ? 1 : 0;
-        e = (int)hipMemcpyAsync(ctx->brick_fp64, inout_host, (size_t)n_bricks, hipMemcpyHostToDevice, ctx->stream);
+        std::vector<unsigned> gmax((size_t)n_bricks);
+        e = (int)hipMemcpyAsync(gmax.data(), ctx->brick_gmax, (size_t)n_bricks * 4, hipMemcpyDeviceToHost, ctx->stream);
+        if (!e) e = (int)hipMemcpyAsync(ctx->brick_fp64, inout_host, (size_t)n_bricks, hipMemcpyHostToDevice, ctx->stream);
         if (!e) e = (int)hipStreamSynchronize(ctx->stream);
         if (e) return hip_fail(ctx, e, "write brick flags");
+        int64_t nf = 0;
+        bool uniform = false;
+        for (int64_t b = 0; b < n_bricks; ++b) {
+            nf += inout_host[b] ? 1 : 0;
+            uniform = uniform || (inout_host[b] && (gmax[(size_t)b] & pbr::kSkipBit));
+        }
         ctx->n_fp64_bricks = nf;
-        ctx->flags_written = true;
+        ctx->flags_uniform = uniform;
     } else {
         e = (int)hipMemcpyAsync(inout_host, ctx->brick_fp64, (size_t)n_bricks, hipMemcpyDeviceToHost, ctx->stream);
         if (!e) e = (int)hipStreamSynchronize(ctx->stream);

@@ -29,7 +29,7 @@ struct pbr_ctx {
     unsigned char *brick_fp64 = nullptr;   // per-brick FP64 flags, device
     pbr::FieldLayout layout{};
     int64_t n_fp64_bricks = 0;
-    bool flags_written = false;            // the FP64 flags are the caller's (pbr_brick_flags), not the calibration's
+    bool flags_uniform = false;            // FP64 flags (of pbr_brick_flags) on bricks without a gradient
     int nx = 0, ny = 0, nz = 0;
     double origin[3] = {0, 0, 0}, spacing[3] = {0, 0, 0};
     double K = 0.0, rho_inf = 0.0;
