@@ -161,7 +161,8 @@ __device__ __forceinline__ int axis_distance(At at, int64_t q, int64_t stride, i
 
 // The whole map of a grid of at most kSkipSmall bricks by one block, in LDS: one launch in place of the five
 // below, which are most of what a small field waits for (pbr_set_density_field with 33^3 nodes 78 -> 39 us, 65^3
-// 76 -> 45; 131 x 100 x 77, 2210 bricks, 98 -> 78).  Beyond, one block's passes would take longer than the launches.
+// 76 -> 45; 131 x 100 x 77, 2210 bricks, 98 -> 78).  With 4096 bricks it takes 64 us against 81 where the gradient is
+// everywhere and 95 against 89 where the gas is uniform, with 5832 bricks 73 against 88 and 119 against 102.
 constexpr int kSkipSmall = 4096;
 __global__ void __launch_bounds__(1024) k_skip_small(unsigned *__restrict__ gmax, int nbx, int nby, int nbz)
 {
