@@ -1483,11 +1483,9 @@ __device__ __forceinline__ void deposit(const TraceParams &P, double x, double y
             if (ii < 0 || ii >= P.W) continue;
             const float cval = 0.5f * (ex[di + 1] - ex[di]) * fy;
             if (!(cval > 0.0f)) continue;
-            // cval * 2^32 is a float exactly, so its half-even integer is too; the conversion saturates
-            // at 2^32 - 1 and the only larger value (the whole light of a ray, 2^32) is put right after
+            // cval * 2^32 is a float exactly, so its half-even integer is too: 32 bits, or the whole light of a ray
             const float v = __builtin_rintf(cval * 4294967296.0f);
-            const unsigned u = (unsigned)v;
-            const unsigned long long q = (unsigned long long)u + (v >= 4294967296.0f ? 1ull : 0ull);
+            const unsigned long long q = v < 4294967296.0f ? (unsigned long long)(unsigned)v : 1ull << 32;
             if (!q) continue;
             if ((unsigned)(ii - win.x0) < (unsigned)win.w && (unsigned)ly < (unsigned)win.h)
                 lds_add_u64(tile + (row + ii), q);
