@@ -29,6 +29,14 @@ __device__ __forceinline__ double index_derivative(const float *rho, int q, int 
     return 0.5 * ((double)rho[q + stride] - (double)rho[q - stride]);
 }
 
+// Between the LDS accesses of a wave's lanes and those of its other lanes to the same places.
+__device__ __forceinline__ void wave_exchange()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // One brick: its density nodes through LDS once, the values of its 9^3 nodes computed once each (and not
 // by each of the up to eight cells around a node), its steepness (largest |grad n| at its nodes) reduced in
 // the block and written without atomics, then the cell records from the node values in LDS.  The 128-byte
@@ -129,7 +137,7 @@ k_field_prep(const float *__restrict__ rho, float4 *__restrict__ out, unsigned *
         // float4 e of cell `lane` at slot e ^ (lane & 7) of the cell: writes and reads spread over the banks
 #pragma unroll
         for (int e = 0; e < kCellFloat4; ++e) stage[wave][lane * kCellFloat4 + (e ^ (lane & 7))] = rec[e];
-        __builtin_amdgcn_wave_barrier();
+        wave_exchange();
         const int cell = lane >> 3, e = lane & 7;  // this lane's cell of a row and part of its record
         if (i0 + cell < nx - 1) {
 #pragma unroll
@@ -140,7 +148,7 @@ k_field_prep(const float *__restrict__ rho, float4 *__restrict__ out, unsigned *
                         kCellFloat4 + e] = v;
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_exchange();
     }
 }
 
