@@ -71,10 +71,12 @@ __global__ void __launch_bounds__(256) k_shadow(const float *__restrict__ p, uns
 // lane's four results are four consecutive units of one sample, so that bias, GELU and the bf16
 // rounding (hardware round-to-nearest-even, two values per instruction) end in one 8-byte LDS
 // store per four values.  Wave w owns units 32 w .. 32 w + 31 of all 128 samples (2 x 8 tiles of
-// 16 x 16): 64 accumulator registers, so that four waves share each SIMD.  Bound by the sum of the products
-// and the vector work (bias, GELU, rounding), which run after one another on a SIMD even in different waves (8
-// products 131 cycles, 4 GELU 137, two waves of each together 532): 2.1e6 rows 1.10 ms, the sum 0.92.  Layer 1 (K = 6, padded to 8)
-// runs in FP32 on the matrix cores (v_mfma_f32_16x16x4_f32, same tiles and result layout).  The
+// 16 x 16): 64 accumulator registers, so that four waves share each SIMD.  Bound by the products and the vector
+// work (bias, GELU, rounding) together, which overlap in part: with four waves per SIMD that alternate 128
+// products (553 cycles per eight of each wave) and 64 GELU (541 per four), both take 882 cycles instead of
+// 1094, 901 with block barriers between; other waves' plain multiply-adds run under products entirely.  2.1e6
+// rows take 1.09 ms; products and vector work 0.92 one after the other, 0.74 overlapped as in that probe.  Layer 1
+// (K = 6, padded to 8) runs in FP32 on the matrix cores (v_mfma_f32_16x16x4_f32, same tiles and result layout).  The
 // output layer is 16 (6 used) x 128, each wave taking 16 samples.
 constexpr int kFuseRows = 128, kActStride = kHidden + 8, kFuseWaves = 8;
 

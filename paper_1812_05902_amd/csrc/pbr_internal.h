@@ -275,7 +275,7 @@ struct BatchConfig {
 };
 
 // Launchers (defined in the .hip files; enqueue on `stream`, return hipError_t as int).
-// Writes the cell records and (atomically) the per-brick max |grad n|; gmax must be zeroed.
+// Writes the field records (per cell, or per node) and every brick's max |grad n|.
 int launch_field_prep(const float *rho, float4 *cells, unsigned *brick_gmax, int nx, int ny, int nz,
                       const double spacing[3], double K, hipStream_t stream, bool nodes = false);
 // Replaces the zeros of gmax by kSkipBit | run << 8 | distance (as a float such a word is not above 0, like

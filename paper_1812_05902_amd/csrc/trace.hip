@@ -1,5 +1,5 @@
-// The per-ray pipeline of sec. 3 in one kernel: emit (3.1) -> integrate through the index grid
-// (3.2, eqs. 3-6) -> aperture and thick lens (3.3, eq. 7) -> sensor hit and erf-integrated
+// The per-ray pipeline of sec. 3 in two kernels.  Integration (k_box*): emission (3.1), then the index grid
+// (3.2, eqs. 3-6).  Finish (k_finish*): aperture and thick lens (3.3, eq. 7), sensor hit and erf-integrated
 // Gaussian spot (3.4, eq. 8), deposited as Q32.32 integers with 64-bit atomics.
 //
 // Precision layout.  The integration inside the box runs in the template type F (float by
@@ -15,7 +15,6 @@ namespace pbr {
 namespace {
 
 constexpr double kTwoPi = 6.283185307179586476925286766559;
-constexpr double kTwoPow32 = 4294967296.0;
 
 // SplitMix64 (Steele, Lea & Flood, OOPSLA 2014) evaluated at counter k: output number k of the
 // generator seeded with `seed`.
@@ -85,7 +84,7 @@ template <> struct CacheOf<double, 0> { using type = CellCache64; };
 // corners of the shared face and loads the other four: half the gather traffic on most crossings.  Every
 // other move loads all eight: with a branch for each of the six faces the few lanes that move sideways
 // cost their wave a pass of loads and copies per face (BOS pair 4.84 -> 4.57 ms, 512^3 shock 48.3 -> 45.5,
-// and 117 instead of 128 registers).
+// and 11 registers fewer).
 __device__ __forceinline__ void gather_nodes(const TraceParams &P, const int ic[3], const int d[3], CellCache &cc)
 {
     const size_t sy = (size_t)P.nx, sz = (size_t)P.nx * (size_t)P.ny;
@@ -1173,7 +1172,7 @@ __global__ void __launch_bounds__(256, NODES ? 4 : 5) k_box32(TraceParams P, Ray
 }
 
 // FP64 integration, bound by VALU issue (every FP64 operation 4.3 cycles per wave).  With the records
-// widened on arrival 149 VGPRs and three waves per SIMD: 500,300 rays through the 64^3 turbulence 2.57 ms
+// widened on arrival 145 VGPRs and three waves per SIMD: 500,300 rays through the 64^3 turbulence 2.57 ms
 // a render, 3.17 with the conversions at each sample (a quarter of the instructions, 172 VGPRs).
 template <bool NODES = false>
 __global__ void __launch_bounds__(256, 3) k_box64(TraceParams P, RayState *__restrict__ st, int64_t n,
@@ -1557,8 +1556,9 @@ __device__ __forceinline__ int wave_min(int v)
 // every pixel of the block is summed in LDS and leaves in one global atomic.  A window fixed around
 // the block's first ray left the rays of its other sources to (2R+1)^2 global atomics each, which is
 // what this kernel waited for wherever sources have few rays.  5e6 rays of 100 per dot 3.25 -> 0.29 ms,
-// 5.2e6 of 1000 per dot 0.87 -> 0.37, 1.7e7 of 2000 per particle 1.38 -> 0.95 (there bound by the FP64
-// optics; its launch constants come divided from the host and the ray's source by multiplication).
+// 5.2e6 of 1000 per dot 0.87 -> 0.37, 1.7e7 of 2000 per particle 1.38 -> 0.95.  There it is bound by VALU issue
+// (busy 83% of the time): 1700 instructions per 64 rays, of which FP64 optics 14%, FP32 (erf) 20% and the rest
+// the integers of the deposit; its LDS additions are waited for 4% of the waves' time.
 enum : int { FEAT_MIE = 1, FEAT_CHAIN = 2 };
 template <int TILE, int RFX = 0, int FEAT = 0>
 __device__ __forceinline__ void finish_block(const TraceParams &P, const RayState *__restrict__ st,
