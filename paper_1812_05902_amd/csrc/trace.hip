@@ -337,7 +337,7 @@ constexpr float kFaceMargin = 1.0e-3f;
 // the same at every step of a straight path and makes up most of the error of a hit (512^3 shock: up to 1e-5 px
 // in T, half that in W).  The node layout keeps T: its images are the ones of 1e8 rays and more, where one ray
 // in 1e9 within 1e-6 px of the sensor's border decides a pixel there (with W, two of eight images of 2e8 rays
-// gained or lost a ray against the increments in T, 5e-3 of the rms pixel; 36.6 ms an image against 37.1).
+// gained or lost a ray against the increments in T, 5e-3 of the rms pixel; an image took 1.4% less).
 template <typename F> struct StepGeom {
     F s[3];                 // cells: h^2 / spacing
     F g[3], gh[3];          // per unit of V in a full step: cells, half of them
@@ -375,19 +375,13 @@ template <typename F, int NODES> __device__ __forceinline__ StepGeom<F> step_geo
     return sg;
 }
 
-// Steps before a ray whose last sample was zero looks for uniform gas (skip_uniform) again: a brick's
-// worth after a look that moved it, twice as many after each look in vain (gas that is uniform only
-// to the rounding of its density has zero samples everywhere and nothing to skip).
-constexpr int kLookSteps = 4;
-
 // The acceleration at the end point of the step before, when that step's last sample serves for it (see
 // rkn_step).
 // D is D_C of the step before in any case (zero before the first step); cached: the base cell's
-// record is loaded; look: steps until a ray whose last sample was zero looks for uniform gas again.
+// record is loaded.
 template <typename F> struct StageCarry {
     F D[3] = {(F)0, (F)0, (F)0};
     bool have = false, cached = false;
-    int look = kLookSteps;
 };
 
 // One step of eqs. 3 and 5 of length lam * h in the parameter t (dR/dt = T, dT/dt = D), in
@@ -503,6 +497,26 @@ __device__ __forceinline__ int run_budget(const TraceParams &P, const StepGeom<F
 // loops: no dynamically indexed arrays.)
 enum : int { STEP_GO = 0, STEP_EXIT = 1, STEP_LIMIT = 2 };
 
+// Word of the map of uniform gas (launch_skip_map) for the brick of a position; p: the position in cells, b:
+// the brick.
+__device__ __forceinline__ unsigned skip_word(const TraceParams &P, const int c[3], const double fd[3], const int last[3],
+                                              double p[3], int b[3])
+{
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        p[a] = (double)c[a] + fd[a];
+        b[a] = min(max((int)floor(p[a]), 0), last[a] - 1) / kBrick;
+    }
+    if (PBR_CHECKED && !access_ok(P, b[0] < P.nbx && b[1] < P.nby && b[2] < P.nbz)) return 0u;
+    return P.skip[((size_t)b[2] * P.nby + b[1]) * P.nbx + b[0]];
+}
+
+// Steps through uniform gas worth leaving the wave for (short of the box's face): a lane that jumps ahead no longer
+// crosses cells with its neighbours, and its jump costs the wave a stretch's look.  15,000 rays past a narrow
+// bump in 100^3 nodes (527 us when every step was taken): 562 us with jumps of any length, 516 from 32 steps on,
+// 425 from 64, 423 from 128; 1e7 rays beside a 256^3 shock 3.66 ms with any, 3.74 from 32, 64 or 128 steps on.
+constexpr int kSkipSteps = 2 * kRunSteps;
+
 // Ray in gas of uniform index.  P.skip holds per brick (kBrick^3 cells) two boxes of bricks without a
 // gradient at any of their nodes (see launch_skip_map): the cube around it that reaches the nearest
 // gradient, and the column of 3 x 3 bricks from it on towards +z.  Within such a box D is exactly zero
@@ -511,17 +525,22 @@ enum : int { STEP_GO = 0, STEP_EXIT = 1, STEP_LIMIT = 2 };
 // face too: the same number of steps.  Cell layout: the same line, without the rounding of each step's
 // increment.  Node layout: each step by the increment that rkn_step rounds (see StepGeom), except where
 // the whole field is uniform: nothing bends a ray there, and it keeps its line to the last bit.
-// Called where the last sample of the ray was zero (or none has been taken).  Returns STEP_EXIT when
-// the ray left the box.
+// Called at the start of a stretch where the last sample of the ray was zero (or none has been taken): once per run
+// of steps, like its neighbours with something to integrate.  Looks every four steps made the rays of a wave
+// wait for runs of unequal length (5e5 rays beside a 353^3 shock 1.36 ms, now 0.54, 1.07 when every step was
+// taken; 2e8 rays beside the 512^3 one 36.9 and 30.8).  Returns STEP_EXIT when the ray left the box.
 // Regions of ambient gas around a flow, the reference render of a BOS pair and the whole volume on
-// either side of a shock are of this kind: the 512^3 shock image (2e8 rays) took 21.7 ms per 1.7e7
-// rays stepping through them (98% of its steps), 2.5 with the cubes alone and 2.2 with the columns: beside
-// a shock along z the cubes are small, and each look costs as much as a step or two.
+// either side of a shock are of this kind: the 512^3 shock image took 21.7 ms per 1.7e7 rays stepping through
+// them (98% of its steps), now 1.63.  The columns matter beside a shock along z, where the cubes are small.
 template <typename F, int NODES>
 __device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], double fd[3], const F Vr[3], const F dV[3],
                                             StageCarry<F> &carry, const StepGeom<F> &sg, int &steps)
 {
     const int *last = sg.last;
+    int b[3];
+    double p[3];
+    unsigned word = skip_word(P, c, fd, last, p, b);
+    if (skip_distance(word) == 0) return STEP_GO;
     const bool rounded = NODES && P.bend32 != 0.0f;
     double W[3];  // cells per step
 #pragma unroll
@@ -531,17 +550,7 @@ __device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], doub
     if (!(fabs(W[0]) + fabs(W[1]) + fabs(W[2]) < 1.0e6)) return STEP_GO;
     const double iW[3] = {1.0 / W[0], 1.0 / W[1], 1.0 / W[2]};
     for (;;) {
-        int b[3];
-        double p[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            p[a] = (double)c[a] + fd[a];
-            b[a] = min(max((int)floor(p[a]), 0), last[a] - 1) / kBrick;
-        }
-        if (PBR_CHECKED && !access_ok(P, b[0] < P.nbx && b[1] < P.nby && b[2] < P.nbz)) return STEP_GO;
-        const unsigned word = P.skip[((size_t)b[2] * P.nby + b[1]) * P.nbx + b[0]];
         const int d = skip_distance(word);
-        if (d == 0) return STEP_GO;
         // bricks the box extends beyond the ray's own: the column where it reaches further ahead
         const int run = W[2] > 0.0 ? skip_run(word) : 0;
         const int side = run > d ? 1 : d - 1, ahead = run > d ? run - 1 : d - 1;
@@ -564,7 +573,7 @@ __device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], doub
         if (ax < 0 || !(s < (double)(P.max_steps - steps))) return STEP_GO;
         // full steps while a whole one stays inside; at a face also the partial step onto it
         const int m = face ? (int)ceil(s) : (int)floor(s * (1.0 - 1.0e-12));
-        if (!face && m < 1) return STEP_GO;
+        if (!face && m < kSkipSteps) return STEP_GO;
         steps += m;
         double l = face ? s : (double)m;
         if (rounded && face) {  // the whole steps, then as the exit rule goes: a step of the rounded fraction, the rest
@@ -584,6 +593,8 @@ __device__ __forceinline__ int skip_uniform(const TraceParams &P, int c[3], doub
         }
         carry.cached = false;
         if (face) return STEP_EXIT;
+        word = skip_word(P, c, fd, last, p, b);
+        if (skip_distance(word) == 0) return STEP_GO;
     }
 }
 
@@ -603,17 +614,12 @@ __device__ __forceinline__ int trace_stretch(const TraceParams &P, C &cc, int c[
                                              Step &step)
 {
     const bool calm = (carry.D[0] == (F)0) & (carry.D[1] == (F)0) & (carry.D[2] == (F)0);
-    if (calm && P.skip) {
-        const int before = steps;
-        if (skip_uniform<F, NODES>(P, c, fd, Vr, dV, carry, sg, steps) == STEP_EXIT) return STEP_EXIT;
-        carry.look = steps > before ? kLookSteps : min(2 * carry.look, kRunSteps);
-    }
+    if (calm && P.skip && skip_uniform<F, NODES>(P, c, fd, Vr, dV, carry, sg, steps) == STEP_EXIT) return STEP_EXIT;
     if (!carry.cached) {
         first_cell<NODES>(P, c, cc);
         carry.cached = true;
     }
     int k = run_budget<F>(P, sg, c, fd, Vr, dV, steps);
-    if (calm && P.skip) k = min(k, carry.look);
     F f[3] = {(F)fd[0], (F)fd[1], (F)fd[2]};
     if (k > 0) {
         steps += k;
