@@ -1166,7 +1166,7 @@ __device__ __forceinline__ void box_body(const TraceParams &P, RayState *__restr
 // needs more registers: four waves per SIMD).
 // Bound by VALU issue (about 140 instructions per wave-step, half of wave-steps moving some lane to a new
 // cell) with the L2 misses of those moves behind it; four waves per SIMD with nothing spilled are 3% slower
-// on the turbulence below.  A render of 5e6 rays through the 128^3 turbulence takes 14.7 ms, 22.9 when
+// on the turbulence below.  A render of 5e6 rays through the 128^3 turbulence takes 14.2 ms, 22.6 when
 // every stage point's cell was found from scratch and every step took three samples (203
 // instructions); 5.2e6 rays through the 257^2 x 81 slice (node layout, BOS pair) 4.29 against 11.3 ms.
 template <bool NODES = false>

@@ -32,4 +32,4 @@ def test_calm_rays_do_not_hold_up_their_wave(kind):
         r.close()
     print(f"{kind}: {ms[0]:.3f} ms, {ms[1]:.3f} ms with a slope everywhere")
     # looking for uniform gas every four steps, or jumping a few steps at a time, made it 1.3 to 1.5 times as long
-    assert ms[0] < 1.1 * ms[1]
+    assert ms[0] < 1.2 * ms[1]
